@@ -417,8 +417,8 @@ qrk_status qrk_get_factor(qrk_handle h, void* Rblk, void* S, void* RB, void* str
 qrk_status qrk_status_get(qrk_handle h, int32_t* detail_host, void* stream);
 
 /* Set the launch shape of the dense-part leaves of a single-problem handle (0 = library
- * default): number of leaves (at most 4096 for float32 handles, 1024 for float64 ones) and,
- * for float64 handles, the tree fan-in.
+ * default): number of leaves (at most 4096 for float32 handles, 1024 for float64 ones); fanin (0 or
+ * 2..64) is accepted and has no effect: the triangles of both types merge in pairs.
  * Not capturable (it may reallocate the merge-tree workspace).  Synchronises the device
  * first (no earlier work on any stream may still read the leaf tables it rewrites).  An LM
  * driver graph captured on this handle before the call is captured again at its next

@@ -64,13 +64,19 @@ struct qrk_handle_s {
   int32_t* leaf_prob = nullptr;  // [leaf_cap]
   int32_t* leaf_idx = nullptr;   // [leaf_cap]
   int64_t leaf_cap = 0;
-  int64_t slot_cap = 0;          // floats
+  int64_t slot_cap = 0;          // elements
   int64_t ctr_cap = 0;           // ints
   int64_t nctr = 1;              // counters in use
-  int32_t* node_l = nullptr;     // pipelined merge tree of a single problem (tree_sep):
-  int32_t* node_r = nullptr;     //   child references of the inner nodes, level order
+  // pipelined merge trees (tree_sep): the inner nodes' problems, indices and child references,
+  // grouped by column-block count, in level order over a count's problems
+  int32_t* node_tab = nullptr;   // one allocation of the four tables
+  int32_t* node_prob = nullptr;
+  int32_t* node_idx = nullptr;
+  int32_t* node_l = nullptr;
+  int32_t* node_r = nullptr;
   int64_t node_cap = 0;
-  int nnodes = 0;                //   0: the merges run inside the leaf launch
+  int node_begin[9] = {0};
+  int node_count[9] = {0};       // all 0: the merges run inside the leaf launch
   int cls_begin[9] = {0};        // float32 leaves grouped by 16-column-block count, widest first
   int queue_begin = 0;           // first leaf of the persistent launch (classes 6 .. 1)
   int64_t qhead_off = 0;         // its queue head among the counters
@@ -95,7 +101,6 @@ struct qrk_handle_s {
   int grid_blocks = 1;
   int refine_grid = 1;
   int leaves = 1;
-  int fanin = 8;
   int64_t ldr = 0;
 
   // owned device workspace
@@ -108,14 +113,7 @@ struct qrk_handle_s {
   void* Sc = nullptr;     // [K][n][nB+1]
   void* Red = nullptr;    // [M][ldr]
   void* RB = nullptr;     // [nB+1][nB+1]
-  void* part0 = nullptr;  // TSQR partial triangles (float64 path): even levels
-  void* part1 = nullptr;  // odd levels
-  int64_t part_cap0 = 0, part_cap1 = 0;  // elements
-  // float64 dense part: every level's workgroups (all problems), level by level
-  qrk::TsqrWg* tsqr_wg = nullptr;
-  int64_t tsqr_wg_cap = 0;
-  std::vector<int> tsqr_lvl_begin, tsqr_lvl_count;
-  float* slots = nullptr; // TSQR tree slots (float32 matrix-core path)
+  void* slots = nullptr;  // dense-part merge slots (stored triangles), in the handle's type
   int* counters = nullptr;
   int max_leaves = 1;
   double* ybuf = nullptr;     // refinement: y_i per block

@@ -30,21 +30,18 @@ hipError_t launch_blockqr_n(const int32_t* blk_list, int64_t begin, int64_t coun
                             const T* B, const int32_t* cam, const T* b, const double* d, const double* lam, T* Rblk,
                             T* Sc, T* Red, const BqrPrologue& pro, const QKeep& qk, hipStream_t st);
 
-// One workgroup of the float64 tall-skinny QR: stream rows [r0, r1) of its input (row
-// stride ldx, L columns) into an L x L upper-triangular R (Householder merges) written
-// row-major at out_off.  Input buffer: in_buf 0 the reduced rows (x_off from Red), 1 or 2 a
-// partial-triangle buffer; output: out_buf 0 the problem's R_B | c_B (in RB), 1 or 2 a
-// partial buffer.  seed >= 0: the leaf starts from diag(sqrt(lam_q) d_B) of problem q = seed.
-struct TsqrWg {
-  int64_t x_off, r0, r1, out_off;
-  int32_t ldx, L, seed;
-  int8_t in_buf, out_buf;
-};
-// One launch per level (count workgroups from wg): the leaves of every problem, then the
-// fanin-way merges of each problem's triangles, level by level; Lmax: the widest problem.
-template <typename T>
-hipError_t launch_tsqr_stream(const TsqrWg* wg, int count, int Lmax, const ProbDesc* probs, int n, const T* Red,
-                              const double* d, const double* lam, T* part0, T* part1, T* RB, hipStream_t st);
+// Float64 tall-skinny QR on the matrix cores (tsqr_f64.hpp) of the problems with ncb column
+// blocks: their leaves (global leaves [leaf_begin, leaf_begin + count) of leaf_prob / leaf_idx), then
+// the inner nodes of their merge trees (entries [node_begin, node_begin + count), in level order
+// over all of them; flags cleared beforehand, two per node and column block).
+int tsqr64_slot_doubles(int L);
+int tsqr64_tile_rows(int ncb);
+hipError_t launch_tsqr64_leaves(int ncb, int leaf_begin, int count, const int32_t* leaf_prob, const int32_t* leaf_idx,
+                                const ProbDesc* probs, int n, const double* Red, const double* d, const double* lam,
+                                double* slots, double* RB, hipStream_t st);
+hipError_t launch_tsqr64_tree(int ncb, int node_begin, int count, const int32_t* node_prob, const int32_t* node_idx,
+                              const int32_t* node_l, const int32_t* node_r, const ProbDesc* probs, double* slots,
+                              int* flags, double* RB, int* status, hipStream_t st);
 
 // Float32 tall-skinny QR on the matrix cores for a batch: the global leaves
 // [cls_begin[c], cls_begin[c] + cls_count[c]) are the leaves of the problems with c

@@ -82,10 +82,8 @@ qrk_status factor_ba(qrk_handle h, hipStream_t st, const double* lam_host = null
   BqrPrologue pro;
   pro.z0 = h->status;
   pro.n0 = h->P;
-  if (std::is_same<T, float>::value) {
-    pro.z1 = h->counters;
-    pro.n1 = h->nctr;
-  }
+  pro.z1 = h->counters;
+  pro.n1 = h->nctr;
   if (lam_host) {
     pro.lam_out = h->lam_d;
     pro.lam_val = *lam_host;
@@ -116,28 +114,35 @@ qrk_status factor_ba(qrk_handle h, hipStream_t st, const double* lam_host = null
   prof_end(h, pr, st);
   if constexpr (std::is_same<T, float>::value) {
     // dense parts on the matrix cores: leaves and merge trees, one launch per column-block count
+    float* slots = static_cast<float*>(h->slots);
     pr = prof_begin(h, 1, st);
     if (launch_tsqr_mfma(h->mode == QRK_BF16X3, h->cls_begin, h->cls_count, h->queue_begin, h->leaf_queue != 0, h->cus,
-                         h->leaf_prob, h->leaf_idx, h->probs_d, h->n, Red, h->d, h->lam_ptr, h->slots, h->counters,
+                         h->leaf_prob, h->leaf_idx, h->probs_d, h->n, Red, h->d, h->lam_ptr, slots, h->counters,
                          h->nctr, h->counters + h->qhead_off, RB, qs, st) != hipSuccess)
       return QRK_EHIP;
-    if (h->nnodes > 0 &&
-        launch_tsqr_tree((h->probs_h[0].L + 15) / 16, h->probs_d, h->node_l, h->node_r, h->nnodes, h->slots,
-                         h->counters, RB, h->status, qs, st) != hipSuccess)
+    const int ncb0 = (h->probs_h[0].L + 15) / 16;
+    if (h->node_count[ncb0] > 0 &&
+        launch_tsqr_tree(ncb0, h->probs_d, h->node_l, h->node_r, h->node_count[ncb0], slots, h->counters, RB,
+                         h->status, qs, st) != hipSuccess)
       return QRK_EHIP;
     prof_end(h, pr, st);
     h->q_valid = keep;
     return QRK_OK;
   }
-  // float64 dense parts: the leaves of every problem in one launch, then one launch per merge
-  // level over every problem still merging (the last level of each writes its R_B | c_B)
-  T* P0 = static_cast<T*>(h->part0);
-  T* P1 = static_cast<T*>(h->part1);
-  for (size_t lv = 0; lv < h->tsqr_lvl_begin.size(); ++lv) {
-    pr = prof_begin(h, lv == 0 ? 1 : 2, st);
-    if (launch_tsqr_stream<T>(h->tsqr_wg + h->tsqr_lvl_begin[lv], h->tsqr_lvl_count[lv], h->max_L, h->probs_d,
-                              h->n, Red, h->d, h->lam_ptr, P0, P1, RB, st) != hipSuccess)
-      return QRK_EHIP;
+  if constexpr (std::is_same<T, double>::value) {
+    // float64 dense parts: leaves and pipelined merge trees, a launch each per column-block count
+    double* slots = static_cast<double*>(h->slots);
+    pr = prof_begin(h, 1, st);
+    for (int c = 8; c >= 1; --c)
+      if (launch_tsqr64_leaves(c, h->cls_begin[c], h->cls_count[c], h->leaf_prob, h->leaf_idx, h->probs_d, h->n, Red,
+                               h->d, h->lam_ptr, slots, RB, st) != hipSuccess)
+        return QRK_EHIP;
+    prof_end(h, pr, st);
+    pr = prof_begin(h, 2, st);
+    for (int c = 8; c >= 1; --c)
+      if (launch_tsqr64_tree(c, h->node_begin[c], h->node_count[c], h->node_prob, h->node_idx, h->node_l, h->node_r,
+                             h->probs_d, slots, h->counters, RB, h->status, st) != hipSuccess)
+        return QRK_EHIP;
     prof_end(h, pr, st);
   }
   return QRK_OK;
@@ -251,114 +256,31 @@ TreeSize tree_size(int64_t leaves) {
   return t;
 }
 
-// Dense-part leaves of every problem.  float32: leaves are single waves; per 16-column-block
-// class c the default is about max(128, rows_c / 4096) rows per leaf (rows_c: the class's
-// reduced plus damping rows), scaled by leaf_scale, at most 1024 leaves per problem; a
-// single-problem handle may fix the count (h->leaves > 0).  Leaves are listed class by class
-// for the per-class launches, and each problem's merge tree gets the slots and arrival
-// counters of tree_size.  float64: leaves are workgroups of about 256 rows.
+// Dense-part leaves of every problem (single waves).  float32: per 16-column-block class c the
+// default is about max(128, rows_c / 4096) rows per leaf (rows_c: the class's reduced plus damping
+// rows), scaled by leaf_scale; float64: a tile of the class, or more in whole tiles so that a
+// class's leaves are about one round of waves.  At most 1024 leaves per problem; a single-problem
+// handle may fix the count (h->leaves > 0).  Leaves are listed class by class for the per-class
+// launches, and each problem's merge tree gets the slots and the arrival counters (or flags) it
+// needs.
 qrk_status assign_leaves(qrk_handle h) {
   std::vector<ProbDesc>& pd = h->probs_h;
   const int P = h->P;
-  if (h->dtype == QRK_F64) {
-    // leaves of about 256 rows (at most 1024 per problem; a batch's problems share about 4096
-    // in proportion to their rows)
-    double rows_all = 0.0;
-    for (const auto& D : pd) rows_all += (double)(D.M + D.nB);
-    for (auto& D : pd) {
-      int64_t def = std::max<int64_t>(1, std::min<int64_t>(ceil_div(D.M + D.nB, 256), 1024));
-      if (P > 1) def = std::min<int64_t>(def, std::max<int64_t>(1, std::llround(4096.0 * (D.M + D.nB) / rows_all)));
-      D.leaves = (int)(h->leaves > 0 ? h->leaves : def);
-      D.rows_per_leaf = std::max<int64_t>(1, ceil_div(D.M, D.leaves));
-    }
-    // the workgroups of every level, all problems together: level 0 streams each problem's
-    // reduced rows into its leaves' triangles, each later level merges fanin triangles of the
-    // level below (stacked as rows); a problem's last level writes its R_B | c_B.  Levels
-    // alternate between the two partial buffers.
-    std::vector<TsqrWg> wl;
-    h->tsqr_lvl_begin.clear();
-    h->tsqr_lvl_count.clear();
-    std::vector<int64_t> G((size_t)P), in_off((size_t)P, 0);
-    for (int q = 0; q < P; ++q) G[(size_t)q] = pd[(size_t)q].leaves;
-    int64_t need[2] = {0, 0};
-    for (int level = 0;; ++level) {
-      const int buf = 1 + (level & 1);  // this level's output buffer when not the root
-      int64_t off = 0;
-      const int begin = (int)wl.size();
-      bool any = false;
-      for (int q = 0; q < P; ++q) {
-        const ProbDesc& D = pd[(size_t)q];
-        const int64_t L = D.L;
-        if (level > 0 && G[(size_t)q] <= 1) continue;  // done
-        const int64_t nout = level == 0 ? G[(size_t)q] : ceil_div(G[(size_t)q], (int64_t)h->fanin);
-        for (int64_t k = 0; k < nout; ++k) {
-          TsqrWg w{};
-          w.L = (int32_t)L;
-          if (level == 0) {
-            w.x_off = D.redoff;
-            w.ldx = (int32_t)D.ldr;
-            w.r0 = std::min<int64_t>(k * D.rows_per_leaf, D.M);
-            w.r1 = std::min<int64_t>((k + 1) * D.rows_per_leaf, D.M);
-            w.seed = k == 0 ? q : -1;
-            w.in_buf = 0;
-          } else {
-            w.x_off = in_off[(size_t)q];
-            w.ldx = (int32_t)L;
-            w.r0 = k * h->fanin * L;
-            w.r1 = std::min<int64_t>((k + 1) * h->fanin, G[(size_t)q]) * L;
-            w.seed = -1;
-            w.in_buf = (int8_t)(1 + ((level - 1) & 1));
-          }
-          if (nout == 1) {
-            w.out_buf = 0;
-            w.out_off = D.rboff;
-          } else {
-            w.out_buf = (int8_t)buf;
-            w.out_off = off + k * L * L;
-          }
-          wl.push_back(w);
-        }
-        if (nout > 1) {
-          in_off[(size_t)q] = off;
-          off += nout * L * L;
-        }
-        G[(size_t)q] = nout;
-        any = true;
-      }
-      if (!any) break;
-      h->tsqr_lvl_begin.push_back(begin);
-      h->tsqr_lvl_count.push_back((int)wl.size() - begin);
-      need[buf - 1] = std::max(need[buf - 1], off);
-    }
-    qrk_status s;
-    const size_t es = sizeof(double);
-    if ((int64_t)wl.size() > h->tsqr_wg_cap) {
-      dfree(h, h->tsqr_wg);
-      h->tsqr_wg = nullptr;
-      h->tsqr_wg_cap = 0;
-      if ((s = dalloc(h, &h->tsqr_wg, sizeof(TsqrWg) * wl.size())) != QRK_OK) return s;
-      h->tsqr_wg_cap = (int64_t)wl.size();
-    }
-    for (int b = 0; b < 2; ++b) {
-      void*& part = b == 0 ? h->part0 : h->part1;
-      int64_t& cap = b == 0 ? h->part_cap0 : h->part_cap1;
-      if (need[b] > cap) {
-        dfree(h, part);
-        part = nullptr;
-        cap = 0;
-        if ((s = dalloc(h, reinterpret_cast<char**>(&part), es * (size_t)need[b])) != QRK_OK) return s;
-        cap = need[b];
-      }
-    }
-    if (!wl.empty() &&
-        hipMemcpy(h->tsqr_wg, wl.data(), sizeof(TsqrWg) * wl.size(), hipMemcpyHostToDevice) != hipSuccess)
-      return QRK_EHIP;
-  } else {
+  const bool f64 = h->dtype == QRK_F64;
+  {
     double rows_cls[9] = {0};
     for (auto& D : pd) rows_cls[(D.L + 15) / 16] += (double)(D.M + D.nB);
     for (auto& D : pd) {
       const int c = (D.L + 15) / 16;
-      const double per = std::max(128.0, rows_cls[c] / 4096.0) * h->leaf_scale;
+      double per;
+      if (f64) {
+        // short tiles (32 and 48 rows at 8 and 7 blocks): at least two, since a merge costs more
+        // than a tile (24,000 rows x 121: 256 leaves 407 us a step, 750 leaves 479)
+        const int tile = tsqr64_tile_rows(c);
+        per = tile * std::max(tile < 64 ? 96.0 / tile : 1.0, std::ceil(rows_cls[c] / (4.0 * h->cus * tile)));
+      } else {
+        per = std::max(128.0, rows_cls[c] / 4096.0) * h->leaf_scale;
+      }
       const int64_t def = std::max<int64_t>(
           1, std::min<int64_t>((int64_t)std::ceil((double)(D.M + D.nB) / std::max(per, 1.0)), 1024));
       D.leaves = (int)(h->leaves > 0 ? h->leaves : def);
@@ -377,36 +299,54 @@ qrk_status assign_leaves(qrk_handle h) {
           }
       h->cls_count[c] = (int)lp.size() - h->cls_begin[c];
     }
-    // a single problem of at most kTreeMaxNCB column blocks merges its leaves in a separate
-    // launch, pipelined over column blocks; otherwise the merges run inside the leaf launch
-    std::vector<int32_t> nl, nr;
-    const bool sep = P == 1 && pd[0].leaves > 1 && (pd[0].L + 15) / 16 <= kTreeMaxNCB;
-    if (sep) {
-      std::vector<int32_t> items((size_t)pd[0].leaves);
-      for (int i = 0; i < pd[0].leaves; ++i) items[(size_t)i] = -1 - i;
-      while (items.size() > 1) {
-        std::vector<int32_t> next;
-        for (size_t i = 0; i + 1 < items.size(); i += 2) {
-          nl.push_back(items[i]);
-          nr.push_back(items[i + 1]);
-          next.push_back((int32_t)nl.size() - 1);
+    // float64 problems and a float32 problem by itself merge their leaves in a separate launch,
+    // pipelined over column blocks; in a float32 batch the merges run inside the leaf launch
+    const bool sep = f64 || P == 1;
+    std::vector<int32_t> np, ni, nl, nr;
+    for (int c = 8; c >= 1; --c) {
+      h->node_begin[c] = (int)np.size();
+      // the trees of the class's problems, level by level over all of them
+      std::vector<std::vector<int32_t>> items((size_t)P);
+      std::vector<int32_t> made((size_t)P, 0);
+      bool any = false;
+      for (int q = 0; q < P; ++q)
+        if (sep && (pd[q].L + 15) / 16 == c && pd[q].leaves > 1) {
+          items[(size_t)q].resize((size_t)pd[q].leaves);
+          for (int i = 0; i < pd[q].leaves; ++i) items[(size_t)q][(size_t)i] = -1 - i;
+          any = true;
         }
-        if (items.size() & 1) next.push_back(items.back());
-        items.swap(next);
+      while (any) {
+        any = false;
+        for (int q = 0; q < P; ++q) {
+          std::vector<int32_t>& it = items[(size_t)q];
+          if (it.size() < 2) continue;
+          std::vector<int32_t> next;
+          for (size_t i = 0; i + 1 < it.size(); i += 2) {
+            np.push_back(q);
+            ni.push_back(made[(size_t)q]);
+            nl.push_back(it[i]);
+            nr.push_back(it[i + 1]);
+            next.push_back(made[(size_t)q]++);
+          }
+          if (it.size() & 1) next.push_back(it.back());
+          it.swap(next);
+          any = any || it.size() > 1;
+        }
       }
+      h->node_count[c] = (int)np.size() - h->node_begin[c];
     }
-    h->nnodes = (int)nl.size();
     int64_t slot = 0, ctr = 0;
     for (auto& D : pd) {
+      const int64_t tri = f64 ? tsqr64_slot_doubles(D.L) : tsqr_mfma_slot_floats(D.L);
       D.slot0 = slot;
       D.ctr0 = ctr;
-      D.tree_sep = sep ? 1 : 0;
-      if (sep) {
-        slot += (int64_t)(D.leaves + h->nnodes) * tsqr_mfma_slot_floats(D.L);
-        ctr += std::max<int64_t>(1, (int64_t)h->nnodes * ((D.L + 15) / 16) * 2);  // two flags per column block
+      D.tree_sep = sep && D.leaves > 1 ? 1 : 0;
+      if (D.tree_sep) {
+        slot += (2 * (int64_t)D.leaves - 1) * tri;
+        ctr += (int64_t)(D.leaves - 1) * ((D.L + 15) / 16) * 2;  // two flags per column block
       } else {
         const TreeSize ts = tree_size(D.leaves);
-        slot += ts.slots * tsqr_mfma_slot_floats(D.L);
+        slot += ts.slots * tri;
         ctr += ts.counters;
       }
     }
@@ -435,21 +375,26 @@ qrk_status assign_leaves(qrk_handle h) {
     h->queue_begin = (int)lp.size();
     for (int c = kQueueNCB; c >= 1; --c)
       if (h->cls_count[c] > 0) h->queue_begin = std::min(h->queue_begin, h->cls_begin[c]);
-    if (h->nnodes > h->node_cap) {
-      dfree(h, h->node_l);
-      dfree(h, h->node_r);
-      h->node_l = h->node_r = nullptr;
+    const int64_t nn = (int64_t)np.size();
+    if (nn > h->node_cap) {
+      dfree(h, h->node_tab);
+      h->node_tab = nullptr;
       h->node_cap = 0;
-      qrk_status s2;
-      if ((s2 = dalloc(h, &h->node_l, sizeof(int32_t) * h->nnodes)) != QRK_OK ||
-          (s2 = dalloc(h, &h->node_r, sizeof(int32_t) * h->nnodes)) != QRK_OK)
-        return s2;
-      h->node_cap = h->nnodes;
+      const qrk_status s2 = dalloc(h, &h->node_tab, sizeof(int32_t) * 4 * (size_t)nn);
+      if (s2 != QRK_OK) return s2;
+      h->node_cap = nn;
     }
-    if (h->nnodes > 0 &&
-        (hipMemcpy(h->node_l, nl.data(), sizeof(int32_t) * nl.size(), hipMemcpyHostToDevice) != hipSuccess ||
-         hipMemcpy(h->node_r, nr.data(), sizeof(int32_t) * nr.size(), hipMemcpyHostToDevice) != hipSuccess))
-      return QRK_EHIP;
+    h->node_prob = h->node_tab;
+    h->node_idx = h->node_tab + nn;
+    h->node_l = h->node_tab + 2 * nn;
+    h->node_r = h->node_tab + 3 * nn;
+    if (nn > 0) {
+      np.insert(np.end(), ni.begin(), ni.end());
+      np.insert(np.end(), nl.begin(), nl.end());
+      np.insert(np.end(), nr.begin(), nr.end());
+      if (hipMemcpy(h->node_tab, np.data(), sizeof(int32_t) * np.size(), hipMemcpyHostToDevice) != hipSuccess)
+        return QRK_EHIP;
+    }
     const int64_t nleaf = (int64_t)lp.size();
     qrk_status s;
     if (nleaf > h->leaf_cap) {
@@ -466,7 +411,9 @@ qrk_status assign_leaves(qrk_handle h) {
       dfree(h, h->slots);
       h->slots = nullptr;
       h->slot_cap = 0;
-      if ((s = dalloc(h, &h->slots, sizeof(float) * slot)) != QRK_OK) return s;
+      if ((s = dalloc(h, reinterpret_cast<char**>(&h->slots), (f64 ? sizeof(double) : sizeof(float)) * (size_t)slot)) !=
+          QRK_OK)
+        return s;
       h->slot_cap = slot;
     }
     if (ctr > h->ctr_cap) {
@@ -765,7 +712,6 @@ qrk_status create_ba(int32_t P, int32_t n, const int32_t* Kp, const int32_t* nBp
   h->grid_blocks = (int)std::min<int64_t>(ceil_div(Ktot, 4), 2048);
   h->max_leaves = dtype == QRK_F32 ? 4096 : 1024;
   h->leaves = 0;
-  h->fanin = 8;
 
   qrk_status s = QRK_OK;
   const int Lm = h->max_L;
@@ -1251,7 +1197,6 @@ qrk_status qrk_set_tsqr_shape(qrk_handle h, int32_t leaves, int32_t fanin) {
   // so nothing that reads them may still be in flight on any stream
   if (hipDeviceSynchronize() != hipSuccess) return QRK_EHIP;
   h->leaves = leaves;
-  h->fanin = fanin ? fanin : 8;
   return assign_leaves(h);
 }
 

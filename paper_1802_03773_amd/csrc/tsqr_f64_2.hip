@@ -1,0 +1,6 @@
+// Instantiation of the float64 tall-skinny QR for 2 column block(s) of 16.
+#include "tsqr_f64.hpp"
+
+namespace qrk {
+QRK_TSQR64_INST(2)
+}  // namespace qrk

@@ -1,0 +1,6 @@
+// Instantiation of the float64 tall-skinny QR for 5 column block(s) of 16.
+#include "tsqr_f64.hpp"
+
+namespace qrk {
+QRK_TSQR64_INST(5)
+}  // namespace qrk
