@@ -7,34 +7,14 @@
 // upper bandwidth w - 1 and a w x w window of R (rows and columns s .. s + w - 1) is all
 // that is live while row i is processed.
 //
-// This file holds the run-time-width kernels, used for 16 <= w <= 31 (bands up to 15 use
-// the compile-time-width kernels of banded_w.hpp), and the kernels shared by every width
-// (J v, J^T r, adjoint entries).
-// Layout of the run-time-width kernels: one problem per group of G = 32 lanes.  Lane l < w
-// holds column s + l of the window (its entries in window rows 0..w-1), lane w holds the
-// right-hand side c of those rows.  The pivot of rotation k is lane k; its two inputs are
-// broadcast to the group, every lane applies the rotation to its own column.
+// This file holds the kernels shared by every width (J v, J^T r, adjoint entries), the dispatch
+// (factor: banded_s.hpp; sweeps: banded_w.hpp up to w = 15, banded_s.hpp above), and run-time-width
+// sweeps for the sizes that those do not take (offsets past 32 bits): one problem per 32 lanes.
 // R is stored banded: row j holds R[j][j .. j + w - 1] (float or double), c is [N].
 #include "qrk_device.hpp"
 #include "qrk_banded.hpp"
 
 namespace qrk {
-
-// Broadcast lane K of each group; shift lanes of a group by one.
-template <int G, int K, typename T>
-__device__ __forceinline__ T gbcast(T x) {
-  if constexpr (G == 16 && sizeof(T) == 4) {
-    return __builtin_bit_cast(T, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x150 + K, 0xF,
-                                                          0xF, false));
-  } else {
-    return __shfl(x, K, G);
-  }
-}
-
-template <int G, typename T>
-__device__ __forceinline__ T gbcast_rt(T x, int k) {
-  return __shfl(x, k, G);
-}
 
 template <int G, typename T>
 __device__ __forceinline__ T gsum(T x) {
@@ -43,111 +23,10 @@ __device__ __forceinline__ T gsum(T x) {
   return x;
 }
 
-// lane l receives lane l + 1's value (within the group; the last lane keeps its own)
-template <int G, typename T>
-__device__ __forceinline__ T from_next(T x) {
-  return __shfl_down(x, 1, G);
-}
-
 // lane l receives lane l - 1's value (the first lane keeps its own)
 template <int G, typename T>
 __device__ __forceinline__ T from_prev(T x) {
   return __shfl_up(x, 1, G);
-}
-
-template <typename T, int G>
-__global__ void __launch_bounds__(256)
-k_banded_givens(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__ row_start,
-                const T* __restrict__ vals, const T* __restrict__ bvec, const double* __restrict__ d,
-                const double* __restrict__ lam, T* __restrict__ Rb, T* __restrict__ cb, int* __restrict__ status) {
-  constexpr int W = G - 1;
-  const int lane = threadIdx.x % G;
-  const int64_t prob = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G;
-  if (prob >= P) return;
-  const double sqrt_lam = sqrt(lam[prob]);
-  const int32_t* rs = row_start + prob * M;
-  const T* V = vals + prob * M * w;
-  const T* bb = bvec + prob * M;
-  const double* dd = d + prob * N;
-  T* R = Rb + prob * N * w;
-  T* cc = cb + prob * N;
-
-  T Rw[W];
-  const T diag0 = (lane < w) ? (T)(sqrt_lam * dd[lane < w ? lane : 0]) : T(0);
-#pragma unroll
-  for (int k = 0; k < W; ++k) Rw[k] = (k == lane) ? diag0 : T(0);
-  int64_t s = 0;
-  bool bad = false;
-
-  auto shift = [&]() {
-    // window row 0 (= row s of R) is final
-    if (lane < w) R[s * w + lane] = Rw[0];
-    if (lane == w) cc[s] = Rw[0];
-#pragma unroll
-    for (int k = 0; k + 1 < W; ++k) Rw[k] = Rw[k + 1];
-    Rw[W - 1] = T(0);
-#pragma unroll
-    for (int k = 0; k < W; ++k) {
-      const T nx = from_next<G>(Rw[k]);
-      if (lane < w - 1) Rw[k] = nx;
-      else if (lane == w - 1) Rw[k] = T(0);
-    }
-    // the new bottom row s + w enters with its damping diagonal
-    if (lane == w - 1) {
-#pragma unroll
-      for (int k = 0; k < W; ++k)
-        if (k == w - 1) Rw[k] = (T)(sqrt_lam * dd[s + w]);
-    }
-    ++s;
-  };
-
-  for (int64_t i = 0; i < M; ++i) {
-    int64_t si = rs[i];
-    if (si < s || si > N - w) {
-      bad = true;
-      si = si < s ? s : (N - w);
-    }
-    while (s < si) shift();
-    T x = T(0);
-    if (lane < w)
-      x = V[i * w + lane];
-    else if (lane == w)
-      x = bb[i];
-    static_for<0, W>([&](auto KK) {
-      constexpr int k = decltype(KK)::value;
-      if (k < w) {
-        const T a = gbcast<G, k>(Rw[k]);
-        const T xk = gbcast<G, k>(x);
-        const T rr = sqrt(a * a + xk * xk);
-        T cs = T(1), sn = T(0);
-        if (rr != T(0)) {
-          const T inv = T(1) / rr;
-          cs = a * inv;
-          sn = xk * inv;
-        }
-        const T Rk = Rw[k];
-        Rw[k] = cs * Rk + sn * x;
-        x = cs * x - sn * Rk;
-        if (lane == k) {
-          Rw[k] = rr;
-          x = T(0);
-        }
-      }
-    });
-  }
-  while (s < N - w) shift();
-  // flush the last window: row s + k holds columns s + k .. s + w - 1 here, zeros beyond
-#pragma unroll
-  for (int k = 0; k < W; ++k) {
-    if (k < w) {
-      if (lane < w) {
-        if (lane >= k) R[(s + k) * w + (lane - k)] = Rw[k];
-        if (lane < k) R[(s + k) * w + (w - k + lane)] = T(0);
-      }
-      if (lane == w) cc[s + k] = Rw[k];
-    }
-  }
-  if (bad) set_status(status, ST_BADINPUT);
 }
 
 // x = R^{-1} rhs for the banded R of every problem (backward sweep).
@@ -384,11 +263,9 @@ hipError_t launch_banded_givens(int P, int64_t M, int64_t N, int w, const int32_
                                 const T* vals, const T* b, const double* d, const double* lam, T* Rb,
                                 T* cb, double* binv, T* R16, int* status, hipStream_t st) {
   if (w < 1 || w > 31) return hipErrorInvalidValue;
-  if (w <= 15) return launch_bgivens_w<T>(P, M, N, w, row_start, vals, b, d, lam, Rb, cb, binv, R16, status, st);
-  const int64_t threads = (int64_t)P * 32;
-  hipLaunchKernelGGL((k_banded_givens<T, 32>), dim3((threads + 255) / 256), dim3(256), 0, st, P, M, N, w, row_start,
-                     vals, b, d, lam, Rb, cb, status);
-  return hipGetLastError();
+  if (w <= 15)
+    return launch_bgivens_s<T, 0>(P, M, N, w, row_start, vals, b, d, lam, Rb, cb, binv, R16, status, st);
+  return launch_bgivens_s<T, 1>(P, M, N, w, row_start, vals, b, d, lam, Rb, cb, binv, nullptr, status, st);
 }
 
 template <typename T>
@@ -396,6 +273,8 @@ hipError_t launch_banded_backsub(int P, int64_t N, int w, const T* Rb, const T* 
                                  double* p, int* status, hipStream_t st) {
   if (R16) {
     return launch_bsweep_w<T>(0, P, N, w, R16, binv, cb, nullptr, p, status, st);
+  } else if (bsweep_x_fits(N, w, sizeof(T))) {
+    return launch_bsweep_x<T>(0, P, N, w, Rb, binv, cb, nullptr, p, status, st);
   } else {
     const int64_t threads = (int64_t)P * 32;
     hipLaunchKernelGGL((k_banded_bwd<T, 32, false>), dim3((threads + 255) / 256), dim3(256), 0, st, P, N, w,
@@ -409,6 +288,8 @@ hipError_t launch_banded_solve_add(int P, int64_t N, int w, const T* Rb, const T
                                    const double* rhs, double* out, hipStream_t st) {
   if (R16) {
     return launch_bsweep_w<T>(1, P, N, w, R16, binv, nullptr, rhs, out, nullptr, st);
+  } else if (bsweep_x_fits(N, w, sizeof(T))) {
+    return launch_bsweep_x<T>(1, P, N, w, Rb, binv, nullptr, rhs, out, nullptr, st);
   } else {
     const int64_t threads = (int64_t)P * 32;
     hipLaunchKernelGGL((k_banded_bwd<T, 32, true>), dim3((threads + 255) / 256), dim3(256), 0, st, P, N, w,
@@ -421,6 +302,7 @@ template <typename T>
 hipError_t launch_banded_fwd(int P, int64_t N, int w, const T* Rb, const T* R16, const double* binv, const double* g,
                              double* y, hipStream_t st) {
   if (R16) return launch_bsweep_w<T>(2, P, N, w, R16, binv, nullptr, g, y, nullptr, st);
+  if (bsweep_x_fits(N, w, sizeof(T))) return launch_bsweep_x<T>(2, P, N, w, Rb, binv, nullptr, g, y, nullptr, st);
   const int64_t threads = (int64_t)P * 32;
   hipLaunchKernelGGL((k_banded_fwd<T, 32>), dim3((threads + 255) / 256), dim3(256), 0, st, P, N, w, Rb, g, y);
   return hipGetLastError();

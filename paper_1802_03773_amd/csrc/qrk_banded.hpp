@@ -55,11 +55,22 @@ inline bool bsweep_w_fits(int64_t P, int64_t N, int w, size_t es) {
   return w >= 1 && w <= 15 && (P * N + 2 * kBandPad) * 16 * (int64_t)es < ((int64_t)1 << 32);
 }
 
-// The compile-time-width kernels (w <= 15, banded_w.hpp); binv: reciprocal pivots [P][N].
+// Givens QR on a ring of lanes (banded_s.hpp): HALF 0 for w = 1 .. 15, HALF 1 for w = 16 .. 31
+// (R16 unused); binv: reciprocal pivots [P][N].
+template <typename T, int HALF>
+hipError_t launch_bgivens_s(int P, int64_t M, int64_t N, int w, const int32_t* row_start, const T* vals, const T* b,
+                            const double* d, const double* lam, T* Rb, T* cb, double* binv, T* R16, int* status,
+                            hipStream_t st);
+// Sweeps for 16 <= w <= 31 on the band itself (kinds as launch_bsweep_w); their offsets into one
+// problem's band are 32-bit.
+inline bool bsweep_x_fits(int64_t N, int w, size_t es) {
+  return w >= 16 && w <= 31 && N >= 1 && N <= ((int64_t)1 << 30) / (w * (int64_t)es);
+}
 template <typename T>
-hipError_t launch_bgivens_w(int P, int64_t M, int64_t N, int w, const int32_t* row_start, const T* vals,
-                            const T* b, const double* d, const double* lam, T* Rb, T* cb, double* binv, T* R16,
-                            int* status, hipStream_t st);
+hipError_t launch_bsweep_x(int kind, int P, int64_t N, int w, const T* Rb, const double* binv, const T* rhsT,
+                           const double* rhsD, double* out, int* status, hipStream_t st);
+
+// The compile-time-width kernels (w <= 15, banded_w.hpp); binv: reciprocal pivots [P][N].
 template <typename T>
 hipError_t launch_bapply_w(int P, int64_t M, int64_t N, int w, const int32_t* row_start, const T* vals, const T* b,
                            const double* v, double* r, hipStream_t st);
