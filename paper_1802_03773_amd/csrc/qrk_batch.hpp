@@ -17,12 +17,13 @@ constexpr int kMaxDense = 128;  // nB + 1 <= 128
 // (a device work queue of leaves, widest problems first); wider ones have a launch per width.
 constexpr int kQueueNCB = 6;
 
-// Dense-part leaves stream tiles of this many rows: 128 up to 4 column blocks and at 6 (there with
-// the running triangle's block rows 1..5 in LDS), 64 at 5, 7 and 8 (a taller tile does not fit
-// the register file there, at 5 not even with the triangle in LDS).  The leaves that store Q keep
-// the triangle in registers and use leaf_tile_rows_keep (the stored tile panels are laid out by
-// it).
-constexpr int leaf_tile_rows(int ncb) { return ncb <= 4 || ncb == 6 ? 128 : 64; }
+// Dense-part leaves stream tiles of this many rows: the tallest that the register file holds next
+// to what it keeps of the running triangle (leaf_lds_rows, tsqr_mfma.hpp), since the fixed work of
+// a panel column (about 285 of its 285 + 3 rows cycles) is spread over the tile's rows.  BF16x3 factor
+// of 600,000 rows: 76 columns (5 blocks) 460 us with 64-row tiles, 411 with 128; 121 columns (8 blocks)
+// 912 us with 64, 782 with 96 rows (128 spill).  The leaves that store Q keep the triangle in
+// registers and use leaf_tile_rows_keep (the stored tile panels are laid out by it).
+constexpr int leaf_tile_rows(int ncb) { return ncb == 8 ? 96 : 128; }
 constexpr int leaf_tile_rows_keep(int ncb) { return ncb <= 4 ? 128 : 64; }
 
 // Stored Q of the float32 dense part: per 16-column panel, T (16 x 16, row-major), the column

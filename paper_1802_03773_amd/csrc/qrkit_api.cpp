@@ -257,8 +257,9 @@ TreeSize tree_size(int64_t leaves) {
 }
 
 // Dense-part leaves of every problem (single waves).  float32: per 16-column-block class c the
-// default is about max(128, rows_c / 4096) rows per leaf (rows_c: the class's reduced plus damping
-// rows), scaled by leaf_scale; float64: a tile of the class, or more in whole tiles so that a
+// default is about max(a tile, rows_c / 4096) rows per leaf (rows_c: the class's reduced plus
+// damping rows; in batches, whose merges use BF16x3 products in that mode, 128 instead of a tile),
+// scaled by leaf_scale; float64: a tile of the class, or more in whole tiles so that a
 // class's leaves are about one round of waves.  At most 1024 leaves per problem; a single-problem
 // handle may fix the count (h->leaves > 0).  Leaves are listed class by class for the per-class
 // launches, and each problem's merge tree gets the slots and the arrival counters (or flags) it
@@ -279,7 +280,7 @@ qrk_status assign_leaves(qrk_handle h) {
         const int tile = tsqr64_tile_rows(c);
         per = tile * std::max(tile < 64 ? 96.0 / tile : 1.0, std::ceil(rows_cls[c] / (4.0 * h->cus * tile)));
       } else {
-        per = std::max(128.0, rows_cls[c] / 4096.0) * h->leaf_scale;
+        per = std::max(P == 1 ? (double)leaf_tile_rows(c) : 128.0, rows_cls[c] / 4096.0) * h->leaf_scale;
       }
       const int64_t def = std::max<int64_t>(
           1, std::min<int64_t>((int64_t)std::ceil((double)(D.M + D.nB) / std::max(per, 1.0)), 1024));

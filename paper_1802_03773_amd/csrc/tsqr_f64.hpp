@@ -415,11 +415,11 @@ k_tsqr64_leaf(int leaf_begin, int nleaves_cls, const int32_t* __restrict__ leaf_
 template <int NCB>
 struct TreeKeep64 {
   static constexpr int off(int p) { return p * kF64Stage + kF64Blk * (p * (p + 1) / 2); }
-  static constexpr int total = off(NCB);
+  static constexpr int total = NCB > 1 ? off(NCB - 1) : 1;  // the last panel is applied to nothing
 };
-// Nodes (waves) per workgroup: as many as the kept panels (32 KiB per wave at 4 column blocks,
-// 100 KiB at 8) leave room for in 160 KiB of LDS, at most four.
-constexpr int tree_waves_f64(int ncb) { return ncb <= 4 ? 4 : (ncb == 5 ? 3 : (ncb <= 7 ? 2 : 1)); }
+// Nodes (waves) per workgroup: as many as the kept panels (20 KiB per wave at 4 column blocks,
+// 75 KiB at 8) leave room for in 160 KiB of LDS, at most four.
+constexpr int tree_waves_f64(int ncb) { return ncb <= 5 ? 4 : (ncb == 6 ? 3 : 2); }
 
 // Published blocks move with device-coherent accesses (sc1), as in tsqr_tree.hpp: the producer
 // waits for its stores before the flag, the consumer reads past the per-XCD L2.

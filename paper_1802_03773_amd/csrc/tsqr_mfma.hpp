@@ -194,6 +194,12 @@ __device__ __forceinline__ void panel_factor(f4& Rd, f4 (&X)[RBN], float (&trow)
     });
     trow[j] = (c < j) ? -tau * t : (c == j ? tau : 0.f);
     if (c == j) sc = scale;
+    // T's column is done before the next column's cross-row sum (volatile asm statements keep their
+    // order): left to the scheduler, the recurrences of later columns pile up at the end of the
+    // panel and hold 20 to 100 registers.  Leaves of 8 column blocks 182 -> 160 us on 176,844 rows x
+    // 127 (no more spills), of 4 45.7 -> 41.9 us on 120,000 x 61, the banded block kernel (2,048
+    // problems) 2.11 -> 1.81 ms; others unchanged.
+    asm volatile("" : "+v"(trow[j]));
   });
 }
 
@@ -648,10 +654,16 @@ __device__ __forceinline__ void tsqr_leaf(int pi, int leaf, const ProbDesc* __re
 }
 
 // Block rows of the running triangle the plain leaf keeps in registers (the rest in LDS): all
-// up to 5 column blocks; at 6 the first (15 blocks in LDS free the registers of its 128-row
-// tiles: 64-row tiles with three rows in registers measured 9% slower on the scale workload); at
-// 7 none and at 8 the first (28 blocks in LDS either way).
-constexpr int leaf_lds_rows(int ncb) { return ncb <= 5 ? ncb : (ncb == 6 ? 1 : (ncb == 7 ? 0 : 1)); }
+// up to 3 column blocks; none at 4, 5 and 7 and the first at 6 and 8, which frees the registers of
+// the taller tiles (leaf_tile_rows).  20 KiB of LDS per wave at 4 blocks, 15 KiB at 6, 30 KiB at 5
+// and 28 KiB at 7 and 8: with the staging at most 152 KiB per workgroup.
+constexpr int leaf_lds_rows(int ncb) {
+  return ncb <= 3 ? ncb : (ncb == 6 || ncb == 8 ? 1 : 0);
+}
+template <int NCB>
+struct LeafTri {
+  static constexpr int blocks = TriSplit<NCB, leaf_lds_rows(NCB)>::lds_blocks;
+};
 
 // One launch per column-block count NCB: wave w is global leaf leaf_begin + w.  The launch
 // that stores Q is a kernel of its own with one more argument; the one without it keeps the
@@ -668,9 +680,6 @@ k_tsqr_mfma(int leaf_begin, int nleaves_cls, const int32_t* __restrict__ leaf_pr
   const int wl = blockIdx.x * 4 + wv;
   if (wl >= nleaves_cls) return;
   if constexpr (leaf_lds_rows(NCB) < NCB) {
-    // 6..8 column blocks: the triangle's later block rows in LDS (15 KiB per wave at 6, 28 KiB
-    // at 7 and 8: 152 KiB per workgroup with the staging), which frees the registers the tile
-    // needs
     constexpr int RL = leaf_lds_rows(NCB);
     __shared__ float rl_all[4][TriSplit<NCB, RL>::lds_blocks * 256];
     tsqr_leaf<NCB, NRB, BF, false, RL>(leaf_prob[leaf_begin + wl], leaf_idx[leaf_begin + wl], probs, n, Red, d,
@@ -745,6 +754,11 @@ __device__ __forceinline__ void tsqr_queue_loop(int nitems, const int32_t* __res
   __shared__ float lds_all[4][kWaveLds];
   const int lane = threadIdx.x & 63;
   float* lds = lds_all[threadIdx.x >> 6];
+  // the triangle rows in LDS, one array for every width (the largest need is that of 6 or 5 blocks)
+  constexpr int kRl = KEEP ? 1 : 256 * (LeafTri<5>::blocks > LeafTri<6>::blocks ? LeafTri<5>::blocks : LeafTri<6>::blocks);
+  static_assert(LeafTri<4>::blocks <= LeafTri<5>::blocks, "the queue's LDS rows");
+  __shared__ float rl_all[4][kRl];
+  float* rl = rl_all[threadIdx.x >> 6];
   for (;;) {
     int item = 0;
     if (lane == 0) item = atomicAdd(qhead, 1);
@@ -755,15 +769,10 @@ __device__ __forceinline__ void tsqr_queue_loop(int nitems, const int32_t* __res
     switch ((probs[pi].L + 15) >> 4) {
 #define QRK_QLEAF(C)                                                                                          \
   case C:                                                                                                     \
-    if constexpr (KEEP) {                                                                                     \
+    if constexpr (KEEP)                                                                                       \
       tsqr_leaf_call_keep<C, BF>(pi, leaf, probs, n, Red, d, lamv, slots, counters, RBall, lds, lane, qs);    \
-    } else if constexpr (leaf_lds_rows(C) < C) {                                                              \
-      __shared__ float rl_all[4][TriSplit<C, leaf_lds_rows(C)>::lds_blocks * 256];                            \
-      tsqr_leaf_call<C, BF>(pi, leaf, probs, n, Red, d, lamv, slots, counters, RBall, lds, lane,              \
-                            rl_all[threadIdx.x >> 6]);                                                        \
-    } else {                                                                                                  \
-      tsqr_leaf_call<C, BF>(pi, leaf, probs, n, Red, d, lamv, slots, counters, RBall, lds, lane, nullptr);    \
-    }                                                                                                         \
+    else                                                                                                      \
+      tsqr_leaf_call<C, BF>(pi, leaf, probs, n, Red, d, lamv, slots, counters, RBall, lds, lane, rl);         \
     break;
       QRK_QLEAF(1) QRK_QLEAF(2) QRK_QLEAF(3) QRK_QLEAF(4) QRK_QLEAF(5) QRK_QLEAF(6)
 #undef QRK_QLEAF

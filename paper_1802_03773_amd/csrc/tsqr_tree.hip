@@ -1,6 +1,5 @@
 // Launch of the pipelined dense-part merge tree (see tsqr_tree.hpp), one instantiation per
-// column-block count up to kTreeMaxNCB = 8 (the kept panels of a wave fit in LDS four waves at a
-// time up to 7 column blocks, 150.5 KiB per workgroup at 7; three at 8, 138 KiB).
+// column-block count up to kTreeMaxNCB = 8.
 #include "qrk_launch.hpp"
 #include "tsqr_tree.hpp"
 
@@ -13,7 +12,7 @@ hipError_t launch_tsqr_tree(int ncb, const ProbDesc* probs, const int32_t* node_
   switch (ncb) {
 #define QRK_TREE(N)                                                                                          \
   case N: {                                                                                                  \
-    constexpr int wpg = tree_waves(N);                                                                       \
+    const int wpg = tree_waves(N, qs.qn != nullptr);                                                         \
     const dim3 grid((unsigned)((nnodes + wpg - 1) / wpg)), blk(64 * wpg);                                    \
     if (qs.qn)                                                                                               \
       hipLaunchKernelGGL((k_tsqr_tree_keep<N>), grid, blk, 0, st, probs, node_l, node_r, nnodes, slots, flags, \

@@ -42,8 +42,8 @@ namespace qrk {
 // Factor the panel [Rd; X[0..RBN-1]]: Rd is the 16x16 diagonal block of the R part, X the
 // tile blocks of this column block (accumulator layout).  On return Rd holds the new diagonal
 // block and R's row j entries, X the raw reflector columns, and T, the scales and W are kept
-// in LDS at `keep`.
-template <int RBN>
+// in LDS at `keep` (STORE).
+template <int RBN, bool STORE = true>
 __device__ __forceinline__ void tree_panel_factor(f4& Rd, f4* X, float* __restrict__ keep, int lane) {
   const int g = lane >> 4;
   const int c = lane & 15;
@@ -57,6 +57,7 @@ __device__ __forceinline__ void tree_panel_factor(f4& Rd, f4* X, float* __restri
 #pragma unroll
     for (int rb = 0; rb < RBN; ++rb) X[rb] = Xp[rb];
   }
+  if constexpr (!STORE) return;
   float* Tl = keep;
   float* Sl = keep + 256;
   float* Wl = keep + 320;
@@ -159,16 +160,24 @@ __device__ __forceinline__ bool tree_wait2(const int* fa, const int* fb, int lan
 // q of a node's output as published above the diagonal, flags[(node * NCB + q) * 2 + 1] its
 // diagonal block.  The root (the last node) writes R_B | c_B row-major.  KEEP (the stored Q):
 // node w's kept panels are written to qs.qn + qn0 + w * TreeKeep<NCB>::total at its end.
-// Waves (nodes) per workgroup: four, or three at 8 column blocks, whose kept panels (46 KiB per
-// wave) fit the 160 KiB of LDS only three at a time.
-constexpr int tree_waves(int ncb) { return ncb <= 7 ? 4 : 3; }
+// A node keeps its panels but the last one (no column block is left to apply that to), unless Q is
+// stored, which takes every panel from LDS.  Waves (nodes) per workgroup: four (150.5 KiB of LDS
+// at 8 column blocks), or three at 8 column blocks with the stored Q (46 KiB each).  Four matter
+// there: a tree of 1,024 leaves has all its nodes resident only with 1,024 waves on the 256 CUs, and
+// with three the upper levels started when whole lower nodes had ended (1,024 leaves x 127 columns:
+// 188 us with three, 138 with four).
+constexpr int tree_waves(int ncb, bool keep) { return ncb <= 7 || !keep ? 4 : 3; }
+template <int NCB, bool KEEP>
+constexpr int tree_lds_floats() {
+  return KEEP ? TreeKeep<NCB>::total : (NCB > 1 ? TreeKeep<NCB>::off(NCB - 1) : 1);
+}
 
 template <int NCB, bool KEEP>
 __device__ __forceinline__ void tsqr_tree_node(const ProbDesc* probs, const int32_t* node_l, const int32_t* node_r,
                                                int nnodes, float* slots, int* flags, float* RBall, int* status,
                                                const QStore& qs) {
-  constexpr int WPG = tree_waves(NCB);
-  __shared__ float keep_all[WPG][TreeKeep<NCB>::total];
+  constexpr int WPG = tree_waves(NCB, KEEP);
+  __shared__ float keep_all[WPG][tree_lds_floats<NCB, KEEP>()];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int node = blockIdx.x * WPG + wv;
@@ -231,7 +240,7 @@ __device__ __forceinline__ void tsqr_tree_node(const ProbDesc* probs, const int3
     // the diagonal block: panel q factored, then published
     wait_children(q, 1);
     load_blocks(q, q, a[q], x[q]);
-    tree_panel_factor<q + 1>(a[q], x, keep + TreeKeep<NCB>::off(q), lane);
+    tree_panel_factor<q + 1, (KEEP || q + 1 < NCB)>(a[q], x, keep + TreeKeep<NCB>::off(q), lane);
     if (root) {
       // column block q of R_B | c_B, row-major L x L (zeros below the diagonal)
       float* Rout = RBall + P.rboff;
