@@ -61,20 +61,19 @@ struct qrk_handle_s {
   int64_t bq_begin[8] = {0};     // per-block QR class (block_classes.hpp): range in blk_list
   int64_t bq_count[8] = {0};
   int32_t* wg_prob = nullptr;    // [nwg]
-  int32_t* leaf_prob = nullptr;  // [leaf_cap]
-  int32_t* leaf_idx = nullptr;   // [leaf_cap]
-  int64_t leaf_cap = 0;
+  int32_t* tab = nullptr;        // one allocation of the leaf and node tables below
+  int64_t tab_cap = 0;
+  int32_t* leaf_prob = nullptr;  // dense-part leaves: problem and index within it
+  int32_t* leaf_idx = nullptr;
   int64_t slot_cap = 0;          // elements
   int64_t ctr_cap = 0;           // ints
   int64_t nctr = 1;              // counters in use
   // pipelined merge trees (tree_sep): the inner nodes' problems, indices and child references,
   // grouped by column-block count, in level order over a count's problems
-  int32_t* node_tab = nullptr;   // one allocation of the four tables
   int32_t* node_prob = nullptr;
   int32_t* node_idx = nullptr;
   int32_t* node_l = nullptr;
   int32_t* node_r = nullptr;
-  int64_t node_cap = 0;
   int node_begin[9] = {0};
   int node_count[9] = {0};       // all 0: the merges run inside the leaf launch
   int cls_begin[9] = {0};        // float32 leaves grouped by 16-column-block count, widest first

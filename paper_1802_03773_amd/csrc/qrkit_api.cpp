@@ -376,38 +376,25 @@ qrk_status assign_leaves(qrk_handle h) {
     h->queue_begin = (int)lp.size();
     for (int c = kQueueNCB; c >= 1; --c)
       if (h->cls_count[c] > 0) h->queue_begin = std::min(h->queue_begin, h->cls_begin[c]);
-    const int64_t nn = (int64_t)np.size();
-    if (nn > h->node_cap) {
-      dfree(h, h->node_tab);
-      h->node_tab = nullptr;
-      h->node_cap = 0;
-      const qrk_status s2 = dalloc(h, &h->node_tab, sizeof(int32_t) * 4 * (size_t)nn);
-      if (s2 != QRK_OK) return s2;
-      h->node_cap = nn;
-    }
-    h->node_prob = h->node_tab;
-    h->node_idx = h->node_tab + nn;
-    h->node_l = h->node_tab + 2 * nn;
-    h->node_r = h->node_tab + 3 * nn;
-    if (nn > 0) {
-      np.insert(np.end(), ni.begin(), ni.end());
-      np.insert(np.end(), nl.begin(), nl.end());
-      np.insert(np.end(), nr.begin(), nr.end());
-      if (hipMemcpy(h->node_tab, np.data(), sizeof(int32_t) * np.size(), hipMemcpyHostToDevice) != hipSuccess)
-        return QRK_EHIP;
-    }
-    const int64_t nleaf = (int64_t)lp.size();
+    // the leaf and node tables: one allocation, one copy
+    const int64_t nn = (int64_t)np.size(), nleaf = (int64_t)lp.size(), nt = 2 * nleaf + 4 * nn;
     qrk_status s;
-    if (nleaf > h->leaf_cap) {
-      dfree(h, h->leaf_prob);
-      dfree(h, h->leaf_idx);
-      h->leaf_prob = h->leaf_idx = nullptr;
-      h->leaf_cap = 0;
-      if ((s = dalloc(h, &h->leaf_prob, sizeof(int32_t) * nleaf)) != QRK_OK ||
-          (s = dalloc(h, &h->leaf_idx, sizeof(int32_t) * nleaf)) != QRK_OK)
-        return s;
-      h->leaf_cap = nleaf;
+    if (nt > h->tab_cap) {
+      dfree(h, h->tab);
+      h->tab = nullptr;
+      h->tab_cap = 0;
+      if ((s = dalloc(h, &h->tab, sizeof(int32_t) * (size_t)nt)) != QRK_OK) return s;
+      h->tab_cap = nt;
     }
+    h->leaf_prob = h->tab;
+    h->leaf_idx = h->leaf_prob + nleaf;
+    h->node_prob = h->leaf_idx + nleaf;
+    h->node_idx = h->node_prob + nn;
+    h->node_l = h->node_idx + nn;
+    h->node_r = h->node_l + nn;
+    for (const auto* v : {&li, &np, &ni, &nl, &nr}) lp.insert(lp.end(), v->begin(), v->end());
+    if (hipMemcpy(h->tab, lp.data(), sizeof(int32_t) * (size_t)nt, hipMemcpyHostToDevice) != hipSuccess)
+      return QRK_EHIP;
     if (slot > h->slot_cap) {
       dfree(h, h->slots);
       h->slots = nullptr;
@@ -424,9 +411,6 @@ qrk_status assign_leaves(qrk_handle h) {
       if ((s = dalloc(h, &h->counters, sizeof(int) * ctr)) != QRK_OK) return s;
       h->ctr_cap = ctr;
     }
-    if (hipMemcpy(h->leaf_prob, lp.data(), sizeof(int32_t) * nleaf, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(h->leaf_idx, li.data(), sizeof(int32_t) * nleaf, hipMemcpyHostToDevice) != hipSuccess)
-      return QRK_EHIP;
   }
   if (hipMemcpy(h->probs_d, pd.data(), sizeof(ProbDesc) * P, hipMemcpyHostToDevice) != hipSuccess)
     return QRK_EHIP;
