@@ -17,150 +17,194 @@
 namespace qrk {
 
 // ---------------------------------------------------------------------------------
-// Dense triangle, one wave: forward (R_B^T y = g) and backward (R_B x = y) sweeps with
-// R_B staged in LDS.  Lane i holds rows i and i + 64 of the right-hand side.
+// Dense triangle, one wave: forward (R_B^T y = g) and backward (R_B x = y) sweeps over the strict
+// upper triangle of R_B, staged in LDS as doubles with an odd row stride.  Lane i holds rows i
+// and i + 64 of the right-hand side.  NBP: nB rounded up to 32, 64, 96 or 128.
+//
+// A sweep is one chain of nB dependent steps, so its time is the latency of a step.  It goes by
+// 16 x 16 blocks of the diagonal: the block's 16 right-hand sides, scaled by the reciprocal
+// diagonal, sit in every 16-lane row of the wave, and a step is one FMA whose broadcast of the
+// solved unknown is the instruction's own lane selection (a broadcast through scalar registers,
+// a multiply and an FMA per step before).  The other rows then take the 16 solved unknowns off
+// with FMAs that do not depend on each other.  Back-substitution of 121 columns 15.0 -> 8.3 us, of
+// 91 columns 13.0 -> 7.6; refinement pass 2 (both sweeps and the sum of the partials) 28 -> 17.9
+// and 24 -> 16.6.
 // ---------------------------------------------------------------------------------
-// R_B (L x L, row-major) into LDS by NT threads: each thread issues all of its loads before
-// its first store, so the copy costs one memory latency rather than one per element.
-template <typename T, int NT>
-__device__ __forceinline__ void stage_dense(const T* __restrict__ RB, int L, float* Rs, double* Rsd, int tid) {
-  constexpr int PER = (kMaxDense * kMaxDense + NT - 1) / NT;
-  const int LL = L * L;
+template <int NBP>
+struct DenseTri {
+  static constexpr int LS = NBP + 1;
+  double r[NBP * LS];  // strict upper triangle, zeros elsewhere
+  double dg[NBP];      // diagonal (1 past nB)
+  double dinv[NBP];    // its reciprocals
+};
+
+// The triangle's elements of one thread of NT: loaded, then stored.  The loads are unconditional
+// (element 0 stands for what is not in the triangle) and the values are selected when they are
+// stored: a load under a condition is waited for before the next one is issued, one memory latency
+// each (back-substitution of 121 columns: 11.0 us with conditional loads, 8.3 without).
+template <typename T, int NBP, int NT>
+struct StageDense {
+  static constexpr int CW = NBP <= 32 ? 32 : (NBP <= 64 ? 64 : 128);  // threads along a row
+  static constexpr int RS = NT / CW;                                   // rows per pass
+  static constexpr int PER = (NBP + RS - 1) / RS;
   T buf[PER];
+  __device__ __forceinline__ void load(const T* __restrict__ RB, int L, int nB, int tid) {
+    const int c = tid & (CW - 1), r0 = tid / CW;
 #pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int e = tid + u * NT;
-    buf[u] = e < LL ? RB[e] : T(0);
-  }
-#pragma unroll
-  for (int u = 0; u < PER; ++u) {
-    const int e = tid + u * NT;
-    if (e < LL) {
-      if constexpr (sizeof(T) == 4)
-        Rs[e] = (float)buf[u];
-      else
-        Rsd[e] = (double)buf[u];
+    for (int u = 0; u < PER; ++u) {
+      const int r = r0 + u * RS;
+      buf[u] = RB[(r <= c && c < nB) ? r * L + c : 0];
     }
   }
+  __device__ __forceinline__ void store(DenseTri<NBP>& D, int nB, int tid) const {
+    const int c = tid & (CW - 1), r0 = tid / CW;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int r = r0 + u * RS;
+      if (c < NBP && r < NBP) {
+        D.r[r * DenseTri<NBP>::LS + c] = r < c && c < nB ? (double)buf[u] : 0.0;
+        if (r == c) D.dg[c] = c < nB ? (double)buf[u] : 1.0;
+      }
+    }
+  }
+};
+
+// Reciprocals of the diagonal, by one wave.
+template <int NBP>
+__device__ __forceinline__ void dense_diag_inv(DenseTri<NBP>& D, int lane) {
+  if (lane < NBP) D.dinv[lane] = 1.0 / D.dg[lane];
+  if (NBP > 64 && lane + 64 < NBP) D.dinv[lane + 64] = 1.0 / D.dg[lane + 64];
+  wave_lds_sync();
 }
 
-template <typename T>
-__device__ __forceinline__ double rs_at(const float* Rs, const double* Rsd, int e) {
-  if constexpr (sizeof(T) == 4)
-    return (double)Rs[e];
+// The steps of a sweep inside a diagonal block: w += (lane K of the 16-lane row's w) r_K for K = 0 ..
+// 14 (FWD) or 15 .. 1.  s_nop 1: a lane selection's source must not have been written by the VALU in
+// the two preceding cycles, which the compiler does not track inside an asm statement.
+#define QRK_SWEEP(OP, K) "s_nop 1\n\tv_fmac_f64_dpp %0, %0, " OP " row_newbcast:" #K " row_mask:0xf bank_mask:0xf\n\t"
+template <bool FWD>
+__device__ __forceinline__ void sweep_steps(double& w, const double (&r)[16]) {
+  if constexpr (FWD)
+    asm(QRK_SWEEP("%1", 0) QRK_SWEEP("%2", 1) QRK_SWEEP("%3", 2) QRK_SWEEP("%4", 3) QRK_SWEEP("%5", 4)
+        QRK_SWEEP("%6", 5) QRK_SWEEP("%7", 6) QRK_SWEEP("%8", 7) QRK_SWEEP("%9", 8) QRK_SWEEP("%10", 9)
+        QRK_SWEEP("%11", 10) QRK_SWEEP("%12", 11) QRK_SWEEP("%13", 12) QRK_SWEEP("%14", 13) QRK_SWEEP("%15", 14)
+        : "+&v"(w)
+        : "v"(r[0]), "v"(r[1]), "v"(r[2]), "v"(r[3]), "v"(r[4]), "v"(r[5]), "v"(r[6]), "v"(r[7]), "v"(r[8]),
+          "v"(r[9]), "v"(r[10]), "v"(r[11]), "v"(r[12]), "v"(r[13]), "v"(r[14]));
   else
-    return Rsd[e];
+    asm(QRK_SWEEP("%15", 15) QRK_SWEEP("%14", 14) QRK_SWEEP("%13", 13) QRK_SWEEP("%12", 12) QRK_SWEEP("%11", 11)
+        QRK_SWEEP("%10", 10) QRK_SWEEP("%9", 9) QRK_SWEEP("%8", 8) QRK_SWEEP("%7", 7) QRK_SWEEP("%6", 6)
+        QRK_SWEEP("%5", 5) QRK_SWEEP("%4", 4) QRK_SWEEP("%3", 3) QRK_SWEEP("%2", 2) QRK_SWEEP("%1", 1)
+        : "+&v"(w)
+        : "v"(r[1]), "v"(r[2]), "v"(r[3]), "v"(r[4]), "v"(r[5]), "v"(r[6]), "v"(r[7]), "v"(r[8]), "v"(r[9]),
+          "v"(r[10]), "v"(r[11]), "v"(r[12]), "v"(r[13]), "v"(r[14]), "v"(r[15]));
+}
+#undef QRK_SWEEP
+// v + sum_K (lane K of the row's w) r_K, in two sums
+template <int K>
+__device__ __forceinline__ void sweep_take4(double& v, double& u, double w, double r0, double r1, double r2,
+                                            double r3) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %2, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %2, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %2, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %2, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf"
+      : "+&v"(v), "+&v"(u)
+      : "v"(w), "v"(r0), "v"(r1), "v"(r2), "v"(r3), "n"(K), "n"(K + 1), "n"(K + 2), "n"(K + 3));
+}
+__device__ __forceinline__ double sweep_take(double v, double w, const double (&r)[16]) {
+  double u = 0.0;
+  sweep_take4<0>(v, u, w, r[0], r[1], r[2], r[3]);
+  sweep_take4<4>(v, u, w, r[4], r[5], r[6], r[7]);
+  sweep_take4<8>(v, u, w, r[8], r[9], r[10], r[11]);
+  sweep_take4<12>(v, u, w, r[12], r[13], r[14], r[15]);
+  return v + u;
 }
 
-__device__ __forceinline__ double read_lane_d(double x, int lane) {
-  const long long b = __builtin_bit_cast(long long, x);
-  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
-}
-
-// Reciprocals of the diagonal of R for rows lane and lane + 64 (1 past nB), computed by all
-// lanes at once so the sweeps below multiply instead of dividing on their critical path.
-template <typename T>
-__device__ __forceinline__ void dense_diag_inv(const float* Rs, const double* Rsd, int L, int nB, int lane,
-                                               double& dv0, double& dv1) {
-  dv0 = lane < nB ? 1.0 / rs_at<T>(Rs, Rsd, lane * L + lane) : 1.0;
-  dv1 = lane + 64 < nB ? 1.0 / rs_at<T>(Rs, Rsd, (lane + 64) * L + lane + 64) : 1.0;
-}
-
-// Forward: y = R^{-T} g (upper-triangular R, column sweep).  v0/v1 hold g for rows lane and
-// lane + 64 on entry and y on exit; dv0/dv1 the reciprocal diagonal.  Step k broadcasts
-// y_k = v_k / R_kk from lane k and takes R_kj y_k off every later row j; a row's value is
-// final once its own step is past, so every lane scales by its reciprocal at the end.  The
-// entries of R for eight steps are read from LDS in one batch (masked to the rows a step
-// updates), so a step waits on no LDS access.
-template <typename T>
-__device__ __forceinline__ void wave_fwd_T(const float* Rs, const double* Rsd, int L, int nB, int lane,
-                                           double dv0, double dv1, double& v0, double& v1) {
-  for (int kb = 0; kb < nB; kb += 8) {
-    double r0[8], r1[8];
+// One sweep, in place: FWD y = R_B^{-T} g, else x = R_B^{-1} y; nblk diagonal blocks hold the nB
+// rows.  A block's LDS reads (its own entries and those of the rows it feeds) are all issued before
+// its steps, so they arrive while the steps run.  Rows that are solved keep their values: the
+// triangle's other half is zeros.  The blocks are a loop, not unrolled: the code runs once per call,
+// and a straight line of it waits on instruction fetch.
+template <int NBP, bool FWD>
+__device__ __forceinline__ void wave_sweep(const DenseTri<NBP>& D, int nblk, int lane, double& v0, double& v1) {
+  constexpr int LS = DenseTri<NBP>::LS;
+  const int c = lane & 15;
+  const int i0 = lane < NBP ? lane : NBP - 1, i1 = lane + 64 < NBP ? lane + 64 : NBP - 1;
+#pragma clang loop unroll(disable)
+  for (int s = 0; s < nblk; ++s) {
+    const int b = FWD ? s : nblk - 1 - s;
+    const bool hi = NBP > 64 && b >= 4;
+    const double* at = D.r + (FWD ? 16 * b * LS : 16 * b);  // entry (k, i) of the block: step k, row i
+    const int sk = FWD ? LS : 1, si = FWD ? 1 : LS;
+    double rd[16], r0[16], r1[16];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int k = kb + u < nB ? kb + u : nB - 1;
-      const double a0 = rs_at<T>(Rs, Rsd, k * L + lane);
-      const double a1 = rs_at<T>(Rs, Rsd, k * L + lane + 64);
-      r0[u] = (lane > k && lane < nB) ? a0 : 0.0;
-      r1[u] = (lane + 64 > k && lane + 64 < nB) ? a1 : 0.0;
-    }
+    for (int k = 0; k < 16; ++k) rd[k] = at[k * sk + (16 * b + c) * si];
+    const double dv = D.dinv[16 * b + c];
+    const uint64_t u = __builtin_bit_cast(uint64_t, hi ? v1 : v0);
+    const int from = ((b & 3) * 16 + c) * 4;  // every 16-lane row takes the block's right-hand sides
+    const unsigned lo = (unsigned)__builtin_amdgcn_ds_bpermute(from, (int)(unsigned)u);
+    const unsigned up = (unsigned)__builtin_amdgcn_ds_bpermute(from, (int)(unsigned)(u >> 32));
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int k = kb + u;
-      if (k < nB) {
-        const double yk = read_lane_d(k < 64 ? v0 * dv0 : v1 * dv1, k & 63);
-        v0 -= r0[u] * yk;
-        v1 -= r1[u] * yk;
-      }
-    }
+    for (int k = 0; k < 16; ++k) r0[k] = at[k * sk + i0 * si];
+    if constexpr (NBP > 64)
+#pragma unroll
+      for (int k = 0; k < 16; ++k) r1[k] = at[k * sk + i1 * si];
+    asm volatile("" ::: "memory");  // the reads above are issued before the steps
+    double w = __builtin_bit_cast(double, ((uint64_t)up << 32) | lo) * dv;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) rd[k] *= -dv;
+    sweep_steps<FWD>(w, rd);
+    const double wn = -w;
+    v0 = sweep_take(v0, wn, r0);
+    if constexpr (NBP > 64) v1 = sweep_take(v1, wn, r1);
+    const bool mine = (lane >> 4) == (b & 3);
+    v0 = mine && !hi ? w : v0;
+    v1 = mine && hi ? w : v1;
   }
-  v0 *= dv0;
-  v1 *= dv1;
-}
-
-// Backward: x = R^{-1} y, columns from the last; the same batching and final scaling.
-template <typename T>
-__device__ __forceinline__ void wave_bwd(const float* Rs, const double* Rsd, int L, int nB, int lane,
-                                         double dv0, double dv1, double& v0, double& v1) {
-  for (int kb = nB - 1; kb >= 0; kb -= 8) {
-    double r0[8], r1[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int k = kb - u >= 0 ? kb - u : 0;
-      const double a0 = rs_at<T>(Rs, Rsd, lane * L + k);
-      const double a1 = rs_at<T>(Rs, Rsd, (lane + 64) * L + k);
-      r0[u] = lane < k ? a0 : 0.0;
-      r1[u] = lane + 64 < k ? a1 : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int k = kb - u;
-      if (k >= 0) {
-        const double xk = read_lane_d(k < 64 ? v0 * dv0 : v1 * dv1, k & 63);
-        v0 -= r0[u] * xk;
-        v1 -= r1[u] * xk;
-      }
-    }
-  }
-  v0 *= dv0;
-  v1 *= dv1;
 }
 
 // ---------------------------------------------------------------------------------
 // Dense part of the back-substitution: R_B p_B = c_B, one workgroup (one working wave)
 // per problem.  c_B is column L-1 of R_B | c_B, or cext (laid out like p) when that is given.
 // ---------------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(256)
+template <typename T, int NBP>
+__global__ void __launch_bounds__(NBP <= 32 ? 256 : 1024)
 k_backsub_dense(const ProbDesc* __restrict__ probs, int n, const T* __restrict__ RBall, double* __restrict__ p,
                 int* __restrict__ status, const double* __restrict__ cext) {
-  __shared__ float Rs[sizeof(T) == 4 ? kMaxDense * kMaxDense : 1];
-  __shared__ double Rsd[sizeof(T) == 8 ? kMaxDense * kMaxDense : 1];
+  constexpr int NT = NBP <= 32 ? 256 : 1024;
+  __shared__ DenseTri<NBP> D;
   const int pi = blockIdx.x;
   const ProbDesc& P = probs[pi];
   const int L = P.L, nB = P.nB;
   const int64_t off = P.noff + P.K * n;
-  stage_dense<T, 256>(RBall + P.rboff, L, Rs, Rsd, threadIdx.x);
+  const T* RB = RBall + P.rboff;
+  const int lane = threadIdx.x & 63;
+  StageDense<T, NBP, NT> stage;
+  stage.load(RB, L, nB, threadIdx.x);
+  // c_B (row 0's when a lane has no row: R_B | c_B has L >= 1 rows and columns)
+  double v0, v1;
+  if (cext) {
+    v0 = cext[nB > 0 ? off + (lane < nB ? lane : 0) : P.noff];
+    v1 = cext[nB > 0 ? off + (lane + 64 < nB ? lane + 64 : 0) : P.noff];
+  } else {
+    const T c0 = RB[(lane < nB ? lane : 0) * L + nB], c1 = RB[(lane + 64 < nB ? lane + 64 : 0) * L + nB];
+    v0 = (double)c0;
+    v1 = (double)c1;
+  }
+  if (lane >= nB) v0 = 0.0;
+  if (lane + 64 >= nB) v1 = 0.0;
+  stage.store(D, nB, threadIdx.x);
   __syncthreads();
   if (threadIdx.x >= 64) return;
-  const int lane = threadIdx.x;
-  double v0 = lane < nB ? (cext ? cext[off + lane] : rs_at<T>(Rs, Rsd, lane * L + nB)) : 0.0;
-  double v1 = lane + 64 < nB ? (cext ? cext[off + lane + 64] : rs_at<T>(Rs, Rsd, (lane + 64) * L + nB)) : 0.0;
-  // largest pivot magnitude: each lane its own diagonal entries, then a wave maximum
-  const double dg0 = lane < nB ? fabs(rs_at<T>(Rs, Rsd, lane * L + lane)) : 0.0;
-  const double dg1 = lane + 64 < nB ? fabs(rs_at<T>(Rs, Rsd, (lane + 64) * L + lane + 64)) : 0.0;
-  const double dmax = wave_allreduce_max(fmax(dg0, dg1));
-  bool bad = false;
-  for (int k = lane; k < nB; k += 64) {
-    const double piv = rs_at<T>(Rs, Rsd, k * L + k);
-    if (is_finite(piv) && !(fabs(piv) > (double)nB * Eps<T>::value * dmax)) bad = true;
-  }
-  double dv0, dv1;
-  dense_diag_inv<T>(Rs, Rsd, L, nB, lane, dv0, dv1);
-  wave_bwd<T>(Rs, Rsd, L, nB, lane, dv0, dv1, v0, v1);
+  // pivots against the largest one: each lane its own diagonal entries, then a wave maximum
+  const double dg0 = lane < nB ? D.dg[lane] : 0.0;
+  const double dg1 = lane + 64 < nB ? D.dg[lane + 64] : 0.0;
+  dense_diag_inv<NBP>(D, lane);
+  wave_sweep<NBP, false>(D, (nB + 15) >> 4, lane, v0, v1);
+  const double dmax = wave_allreduce_max(fmax(fabs(dg0), fabs(dg1)));
+  const double tol = (double)nB * Eps<T>::value * dmax;
+  const bool bad = (lane < nB && is_finite(dg0) && !(fabs(dg0) > tol)) ||
+                   (lane + 64 < nB && is_finite(dg1) && !(fabs(dg1) > tol));
   bool nonfinite = false;
   if (lane < nB) {
     p[off + lane] = v0;
@@ -174,11 +218,29 @@ k_backsub_dense(const ProbDesc* __restrict__ probs, int n, const T* __restrict__
   if (nonfinite) set_status(status + pi, ST_NONFINITE);
 }
 
+// f(NBP) for the smallest triangle size that holds max_L - 1 coupled columns
+template <typename F>
+static void dense_size(int max_L, F&& f) {
+  const int nB = max_L - 1;
+  if (nB <= 32)
+    f(std::integral_constant<int, 32>{});
+  else if (nB <= 64)
+    f(std::integral_constant<int, 64>{});
+  else if (nB <= 96)
+    f(std::integral_constant<int, 96>{});
+  else
+    f(std::integral_constant<int, 128>{});
+}
+
 template <typename T>
 hipError_t launch_backsub_dense(const BatchView& bv, const T* RB, double* p, int* status, hipStream_t st,
                                 const double* cext) {
   if (bv.max_L > kMaxDense) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_backsub_dense<T>), dim3(bv.P), dim3(256), 0, st, bv.probs, bv.n, RB, p, status, cext);
+  dense_size(bv.max_L, [&](auto S) {
+    constexpr int NBP = decltype(S)::value;
+    hipLaunchKernelGGL((k_backsub_dense<T, NBP>), dim3(bv.P), dim3(NBP <= 32 ? 256 : 1024), 0, st, bv.probs, bv.n,
+                       RB, p, status, cext);
+  });
   return hipGetLastError();
 }
 
@@ -640,14 +702,15 @@ hipError_t launch_refine_residual(const BatchView& bv, const T* A, const T* B, c
 // ADJ = true : adjoint (rhs = g_B + sum of partials; the solution -> u_B in out, laid out
 //              like p; p untouched).
 // ---------------------------------------------------------------------------------
-template <typename T, bool ADJ>
+template <typename T, bool ADJ, int NBP>
 __global__ void __launch_bounds__(1024)
 k_refine_dense(const ProbDesc* __restrict__ probs, int n, const double* __restrict__ part,
                const T* __restrict__ RBall, const double* __restrict__ dvec, const double* __restrict__ lamv,
                double* __restrict__ p, double* __restrict__ out, const double* __restrict__ gvec) {
-  __shared__ float Rs[sizeof(T) == 4 ? kMaxDense * kMaxDense : 1];
-  __shared__ double Rsd[sizeof(T) == 8 ? kMaxDense * kMaxDense : 1];
-  __shared__ double acc[8][kMaxDense];
+  using Stage = StageDense<T, NBP, 1024>;
+  constexpr int CW = Stage::CW, G = 1024 / CW;
+  __shared__ DenseTri<NBP> D;
+  __shared__ double acc[G][CW];
   const int pi = blockIdx.x;
   const ProbDesc& P = probs[pi];
   const int nB = P.nB, L = P.L;
@@ -655,63 +718,58 @@ k_refine_dense(const ProbDesc* __restrict__ probs, int n, const double* __restri
   const double* pp = part + (int64_t)P.wg0 * kMaxDense;
   const int nparts = P.nwg;
   const int t = threadIdx.x;
-  const int j = t & 127, q = t >> 7;
-  // partials of group q: w = q, q + 8, ...; loaded 32 at a time so the loads overlap, then
+  const int lane = t & 63;
+  const bool on0 = lane < nB, on1 = lane + 64 < nB;
+  Stage stage;
+  stage.load(RBall + P.rboff, L, nB, t);
+  // the first wave's part of the right-hand side and of p_B
+  // (an unknown of the problem stands in where a lane has none; N >= 1)
+  const int64_t e0 = on0 ? off + lane : P.noff, e1 = on1 ? off + lane + 64 : P.noff;
+  const double* dsrc = ADJ ? gvec : dvec;
+  const double d0 = dsrc[e0], d1 = dsrc[e1];
+  const double p0 = ADJ ? 0.0 : p[e0], p1 = ADJ ? 0.0 : p[e1];
+  const double lam = ADJ ? 0.0 : lamv[pi];
+  // partials of group q: w = q, q + G, ...; loaded up to 32 at a time so the loads overlap, then
   // added in order
+  const int j = t & (CW - 1), q = t / CW;
   double s = 0.0;
   if (j < nB) {
-    for (int w0 = q; w0 < nparts; w0 += 8 * 32) {
+    for (int w0 = q; w0 < nparts; w0 += G * 32) {
       double buf[32];
 #pragma unroll
       for (int u = 0; u < 32; ++u) {
-        const int w = w0 + 8 * u;
-        buf[u] = w < nparts ? pp[(int64_t)w * kMaxDense + j] : 0.0;
+        const int w = w0 + G * u;
+        buf[u] = pp[(int64_t)(w < nparts ? w : q) * kMaxDense + j];
       }
 #pragma unroll
-      for (int u = 0; u < 32; ++u) s += buf[u];
+      for (int u = 0; u < 32; ++u) s += w0 + G * u < nparts ? buf[u] : 0.0;
     }
   }
   acc[q][j] = s;
-  stage_dense<T, 1024>(RBall + P.rboff, L, Rs, Rsd, t);
+  stage.store(D, nB, t);
   __syncthreads();
   if (t >= 64) return;
-  const int lane = t;
-  const double lam = ADJ ? 0.0 : lamv[pi];
+  double g0 = 0.0, g1 = 0.0;
+#pragma unroll
+  for (int k = 0; k < G; ++k) {
+    g0 += acc[k][lane & (CW - 1)];
+    if (CW > 64) g1 += acc[k][(lane + 64) & (CW - 1)];
+  }
   double v0 = 0.0, v1 = 0.0;
-  if (lane < nB) {
-    double g = 0.0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) g += acc[k][lane];
-    if (ADJ) {
-      v0 = gvec[off + lane] + g;
-    } else {
-      const double dj = dvec[off + lane];
-      v0 = g - lam * dj * dj * p[off + lane];
-    }
-  }
-  if (lane + 64 < nB) {
-    double g = 0.0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) g += acc[k][lane + 64];
-    if (ADJ) {
-      v1 = gvec[off + lane + 64] + g;
-    } else {
-      const double dj = dvec[off + lane + 64];
-      v1 = g - lam * dj * dj * p[off + lane + 64];
-    }
-  }
-  double dv0, dv1;
-  dense_diag_inv<T>(Rs, Rsd, L, nB, lane, dv0, dv1);
-  wave_fwd_T<T>(Rs, Rsd, L, nB, lane, dv0, dv1, v0, v1);
-  wave_bwd<T>(Rs, Rsd, L, nB, lane, dv0, dv1, v0, v1);
+  if (on0) v0 = ADJ ? d0 + g0 : g0 - lam * d0 * d0 * p0;
+  if (on1) v1 = ADJ ? d1 + g1 : g1 - lam * d1 * d1 * p1;
+  const int nblk = (nB + 15) >> 4;
+  dense_diag_inv<NBP>(D, lane);
+  wave_sweep<NBP, true>(D, nblk, lane, v0, v1);
+  wave_sweep<NBP, false>(D, nblk, lane, v0, v1);
   double* o = ADJ ? out + off : out + (int64_t)pi * kMaxDense;
-  if (lane < nB) {
+  if (on0) {
     o[lane] = v0;
-    if (!ADJ) p[off + lane] += v0;
+    if (!ADJ) p[off + lane] = p0 + v0;
   }
-  if (lane + 64 < nB) {
+  if (on1) {
     o[lane + 64] = v1;
-    if (!ADJ) p[off + lane + 64] += v1;
+    if (!ADJ) p[off + lane + 64] = p1 + v1;
   }
 }
 
@@ -719,8 +777,10 @@ template <typename T>
 hipError_t launch_refine_dense(const BatchView& bv, const double* part, const T* RB, const double* dvec,
                                double* p, double* delta_B, hipStream_t st) {
   if (bv.max_L > kMaxDense) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_refine_dense<T, false>), dim3(bv.P), dim3(1024), 0, st, bv.probs, bv.n, part, RB, dvec,
-                     bv.lam, p, delta_B, (const double*)nullptr);
+  dense_size(bv.max_L, [&](auto S) {
+    hipLaunchKernelGGL((k_refine_dense<T, false, decltype(S)::value>), dim3(bv.P), dim3(1024), 0, st, bv.probs, bv.n,
+                       part, RB, dvec, bv.lam, p, delta_B, (const double*)nullptr);
+  });
   return hipGetLastError();
 }
 
@@ -728,8 +788,10 @@ template <typename T>
 hipError_t launch_adjoint_dense(const BatchView& bv, const double* part, const T* RB, const double* g, double* u,
                                 hipStream_t st) {
   if (bv.max_L > kMaxDense) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_refine_dense<T, true>), dim3(bv.P), dim3(1024), 0, st, bv.probs, bv.n, part, RB,
-                     (const double*)nullptr, bv.lam, (double*)nullptr, u, g);
+  dense_size(bv.max_L, [&](auto S) {
+    hipLaunchKernelGGL((k_refine_dense<T, true, decltype(S)::value>), dim3(bv.P), dim3(1024), 0, st, bv.probs, bv.n,
+                       part, RB, (const double*)nullptr, bv.lam, (double*)nullptr, u, g);
+  });
   return hipGetLastError();
 }
 
