@@ -77,6 +77,30 @@ __device__ __forceinline__ void bqr_prologue(const BqrPrologue& pro) {
   if (threadIdx.x == 0 && pro.lam_out) *pro.lam_out = pro.lam_val;
 }
 
+// Flags between the nodes of a pipelined merge tree: flag 2 q + k of a node says that part k (0: above
+// the diagonal, 1: the diagonal block) of its column block q is published.  A look reads both parts'
+// flags of both children (fa, fb) in one device-scope load, a lane each, so a round trip to memory
+// answers all four; it is issued before the work that comes ahead of the wait, which then usually finds
+// the answer there.
+__device__ __forceinline__ int tree_look(const int* fa, const int* fb, int q, int lane) {
+  return __hip_atomic_load(((lane & 1) ? fb : fa) + 2 * q + ((lane >> 1) & 1), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+}
+// Part k published by both children, as of the look v?
+__device__ __forceinline__ bool tree_seen(int v, int k) {
+  return (__builtin_amdgcn_ballot_w64(v == 0) & (k ? 0xccccccccccccccccull : 0x3333333333333333ull)) == 0;
+}
+// Wait (bounded) until it is; false on timeout.
+__device__ __forceinline__ bool tree_wait(int& v, const int* fa, const int* fb, int q, int k, int lane) {
+#pragma clang loop unroll(disable)
+  for (int it = 0; it < (1 << 21); ++it) {
+    if (tree_seen(v, k)) return true;
+    __builtin_amdgcn_s_sleep(1);
+    v = tree_look(fa, fb, q, lane);
+  }
+  return false;
+}
+
 __device__ __forceinline__ void set_status(int* status, int bits) {
   if (status) atomicOr(status, bits);
 }

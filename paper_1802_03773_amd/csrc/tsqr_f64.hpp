@@ -445,21 +445,6 @@ __device__ __forceinline__ d4 tree_load64(const double* src, int lane) {
   r[3] = __builtin_bit_cast(double, ((uint64_t)hi[3] << 32) | hi[2]);
   return r;
 }
-// Wait (bounded) until both flags are set (null counts as set); false on timeout.
-__device__ __forceinline__ bool tree_wait64(const int* fa, const int* fb, int lane) {
-  for (int it = 0; it < (1 << 20); ++it) {
-    int ready = 1;
-    if (lane == 0) {
-      const int va = fa ? __hip_atomic_load(fa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 1;
-      const int vb = fb ? __hip_atomic_load(fb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 1;
-      ready = (va != 0) && (vb != 0);
-    }
-    if (__builtin_amdgcn_readfirstlane(ready) != 0) return true;
-    __builtin_amdgcn_s_sleep(2);
-  }
-  return false;
-}
-
 // One wave per inner node of the trees of every problem with NCB column blocks: wave w runs node
 // entry node_begin + w, node node_idx of problem node_prob with children node_l / node_r (>= 0 a
 // node of the same problem, < 0 its leaf -1 - r).  The entries are in level order over all the
@@ -510,19 +495,29 @@ k_tsqr64_tree(int node_begin, int nnodes, const int32_t* __restrict__ node_prob,
     if (lane == 0)
       __hip_atomic_store(pflags + ((int64_t)node * NCB + q) * 2 + k, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
+  // the children's flags (a leaf child counts as published: the other child's flags stand in)
+  const bool inner = lref >= 0 || rref >= 0;
+  const int* fl = pflags + (int64_t)(lref >= 0 ? lref : rref) * NCB * 2;
+  const int* fr = pflags + (int64_t)(rref >= 0 ? rref : lref) * NCB * 2;
+  int seen = inner ? tree_look(fl, fr, 0, lane) : 1;
   auto wait_children = [&](int q, int k) {
-    if (!stalled && (lref >= 0 || rref >= 0))
-      stalled = !tree_wait64(lref >= 0 ? pflags + ((int64_t)lref * NCB + q) * 2 + k : nullptr,
-                             rref >= 0 ? pflags + ((int64_t)rref * NCB + q) * 2 + k : nullptr, lane);
+    if (!stalled && inner) stalled = !tree_wait(seen, fl, fr, q, k, lane);
     asm volatile("" ::: "memory");  // the block's loads stay after the flags were seen
   };
   static_for<0, NCB>([&](auto QQ) {
     constexpr int q = decltype(QQ)::value;
+    bool have_diag = false;
     if constexpr (q > 0) {
-      // above the diagonal: panels 0..q-1 applied, then published
+      // above the diagonal: panels 0..q-1 applied, then published (the diagonal block is loaded here
+      // too when it is there already)
       wait_children(q, 0);
+      have_diag = stalled || tree_seen(seen, 1);
 #pragma unroll
       for (int p = 0; p < q; ++p) load_blocks(p, q, a[p], x[p]);
+      if (have_diag)
+        load_blocks(q, q, a[q], x[q]);
+      else
+        seen = tree_look(fl, fr, q, lane);
       static_for<0, q>([&](auto PP) {
         constexpr int p = decltype(PP)::value;
         const double* kp = keep + TreeKeep64<NCB>::off(p);
@@ -552,8 +547,11 @@ k_tsqr64_tree(int node_begin, int nnodes, const int32_t* __restrict__ node_prob,
       }
     }
     // the diagonal block: panel q factored, then published
-    wait_children(q, 1);
-    load_blocks(q, q, a[q], x[q]);
+    if (!have_diag) {
+      wait_children(q, 1);
+      load_blocks(q, q, a[q], x[q]);
+    }
+    if (q + 1 < NCB && inner) seen = tree_look(fl, fr, q + 1, lane);
     {
       double trow[16], sc;
       d4 Xp[q + 1];

@@ -137,23 +137,6 @@ __device__ __forceinline__ f4 tree_load_block(const float* src, int lane) {
   return __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, 0, kCoherent);
 }
 
-// Wait (bounded) until both *fa and *fb are set (a null flag counts as set); false on
-// timeout.  Lane 0 polls with relaxed device-scope loads (no cache invalidation per poll),
-// both flags in the same round trip.
-__device__ __forceinline__ bool tree_wait2(const int* fa, const int* fb, int lane) {
-  for (int it = 0; it < (1 << 20); ++it) {
-    int ready = 1;
-    if (lane == 0) {
-      const int va = fa ? __hip_atomic_load(fa, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 1;
-      const int vb = fb ? __hip_atomic_load(fb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 1;
-      ready = (va != 0) && (vb != 0);
-    }
-    if (__builtin_amdgcn_readfirstlane(ready) != 0) return true;
-    __builtin_amdgcn_s_sleep(2);
-  }
-  return false;
-}
-
 // One wave per inner node of the (single) problem's tree.  node_l / node_r: child references,
 // r >= 0 an inner node, r < 0 leaf -1 - r.  Leaf triangles are at slots 0 .. leaves-1 of the
 // problem, node outputs at slots leaves + node; flags[(node * NCB + q) * 2] marks column block
@@ -214,19 +197,29 @@ __device__ __forceinline__ void tsqr_tree_node(const ProbDesc* probs, const int3
     if (lane == 0)
       __hip_atomic_store(pflags + ((int64_t)node * NCB + q) * 2 + k, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
+  // the children's flags (a leaf child counts as published: the other child's flags stand in)
+  const bool inner = lref >= 0 || rref >= 0;
+  const int* fl = pflags + (int64_t)(lref >= 0 ? lref : rref) * NCB * 2;
+  const int* fr = pflags + (int64_t)(rref >= 0 ? rref : lref) * NCB * 2;
+  int seen = inner ? tree_look(fl, fr, 0, lane) : 1;
   auto wait_children = [&](int q, int k) {
-    if (!stalled && (lref >= 0 || rref >= 0))
-      stalled = !tree_wait2(lref >= 0 ? pflags + ((int64_t)lref * NCB + q) * 2 + k : nullptr,
-                            rref >= 0 ? pflags + ((int64_t)rref * NCB + q) * 2 + k : nullptr, lane);
+    if (!stalled && inner) stalled = !tree_wait(seen, fl, fr, q, k, lane);
     asm volatile("" ::: "memory");  // the block's loads stay after the flags were seen
   };
   static_for<0, NCB>([&](auto QQ) {
     constexpr int q = decltype(QQ)::value;
+    bool have_diag = false;
     if constexpr (q > 0) {
-      // above the diagonal: panels 0..q-1 applied, then published
+      // above the diagonal: panels 0..q-1 applied, then published (the diagonal block is loaded here
+      // too when it is there already)
       wait_children(q, 0);
+      have_diag = stalled || tree_seen(seen, 1);
 #pragma unroll
       for (int p = 0; p < q; ++p) load_blocks(p, q, a[p], x[p]);
+      if (have_diag)
+        load_blocks(q, q, a[q], x[q]);
+      else
+        seen = tree_look(fl, fr, q, lane);
       static_for<0, q>([&](auto PP) {
         constexpr int p = decltype(PP)::value;
         tree_panel_apply<p + 1>(keep + TreeKeep<NCB>::off(p), a[p], x, lane);
@@ -238,8 +231,11 @@ __device__ __forceinline__ void tsqr_tree_node(const ProbDesc* probs, const int3
       }
     }
     // the diagonal block: panel q factored, then published
-    wait_children(q, 1);
-    load_blocks(q, q, a[q], x[q]);
+    if (!have_diag) {
+      wait_children(q, 1);
+      load_blocks(q, q, a[q], x[q]);
+    }
+    if (q + 1 < NCB && inner) seen = tree_look(fl, fr, q + 1, lane);
     tree_panel_factor<q + 1, (KEEP || q + 1 < NCB)>(a[q], x, keep + TreeKeep<NCB>::off(q), lane);
     if (root) {
       // column block q of R_B | c_B, row-major L x L (zeros below the diagonal)
