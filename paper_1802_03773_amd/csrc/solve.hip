@@ -244,10 +244,43 @@ hipError_t launch_backsub_dense(const BatchView& bv, const T* RB, double* p, int
   return hipGetLastError();
 }
 
-// Raw buffer load of one element: the descriptor holds the wave-uniform row-block base, the
-// row offset is the scalar offset and the lane's column offset the vector offset.  Word 3
-// is the gfx9 raw-buffer format; the record count only bounds the range check, and every
-// offset used stays inside the rows of the pack.
+// ---------------------------------------------------------------------------------
+// Rows of a pack (B's or S|c's) streamed through registers.  A row of at most CW columns (16, 32,
+// 64 or 128, chosen per problem) takes min(CW, 64) lanes, so one load moves RPL = 1, 2 or 4 whole
+// rows and a chunk of NV loads CHR = NV RPL rows: narrow dense parts use all lanes of a load.
+// Lane (g, col): column col (and col + 64 at CW = 128) of rows i RPL + g.
+//
+// Row sums (B p_B, S v): every lane multiplies its values by its columns' entries, and the NV sums
+// are folded across the lanes of a row in halving steps: a step adds two lanes' values for one half
+// of the rows in one of the lanes and for the other half in the other, so NV values cost NV - 1
+// folds, and each lane ends with one row's sum.  (Before, the chunk went through LDS transposed
+// and each row was summed by four lanes: 128 columns of p_B per lane, 64 registers, held one wave
+// less per SIMD.)  All sums run in a fixed order.  Bound: instruction issue and, in large problems, the
+// stream itself.  Refinement pass 1 of 50,000 blocks of 12 x 3 with 91 columns 71 -> 54 us (3.2 -> 4.2
+// TB/s), of 128 ragged problems with 6, 30 or 90 columns 1,670 -> 1,006 us; block solves there 275 -> 91
+// us (units of 64 / n blocks instead of packs of 64 rows, and one load for up to four rows).
+// ---------------------------------------------------------------------------------
+template <typename T, int CW>
+struct RowStream {
+  static constexpr int LN = CW < 64 ? CW : 64;  // lanes of a row
+  static constexpr int RPL = 64 / LN;
+  static constexpr int NV = sizeof(T) == 4 ? 16 : 8;
+  static constexpr int SL = CW > 64 ? 2 : 1;
+  static constexpr int CHR = NV * RPL;
+  // row of a chunk whose sum the lane holds after fold_rows
+  static __device__ __forceinline__ int sum_row(int lane) {
+    return ((lane & (LN - 1)) / (LN / NV)) * RPL + lane / LN;
+  }
+};
+
+template <typename T, int CW>
+using StreamChunk = T[RowStream<T, CW>::SL][RowStream<T, CW>::NV];
+
+// Raw buffer load of one element: the descriptor holds the wave-uniform base, the row offset is the
+// scalar offset and the lane's column (and row of the load) the vector offset.  Word 3 is the gfx9
+// raw-buffer format; the record count only bounds the range check, and every offset used stays
+// inside the rows of the pack, or is kNoColumn, which the range check answers with zero.
+constexpr uint32_t kNoColumn = 0x80000000u;
 template <typename T>
 __device__ __forceinline__ T buf_ld_row(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) {
   if constexpr (sizeof(T) == 4)
@@ -256,112 +289,199 @@ __device__ __forceinline__ T buf_ld_row(__amdgpu_buffer_rsrc_t rs, uint32_t voff
     return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)voff, (int)soff, 0));
 }
 
+// Loads one chunk (rows c0 .. of `rows` rows of stride ld, ncol columns); rows past the last one
+// re-read it.
+template <typename T, int CW>
+__device__ __forceinline__ void stream_load(StreamChunk<T, CW>& v,
+                                            __amdgpu_buffer_rsrc_t rs, int c0, int rows, int ld, int ncol, int lane) {
+  using S = RowStream<T, CW>;
+  const int g = lane / S::LN, col = lane & (S::LN - 1);
+  const int lastg = (rows - 1) / S::RPL * S::RPL;  // first row of the last load that holds a row
+  const int gl = lastg + g < rows ? g : rows - 1 - lastg;
+  const uint32_t full = (uint32_t)(g * ld + col) * (uint32_t)sizeof(T);
+  const uint32_t last = (uint32_t)(gl * ld + col) * (uint32_t)sizeof(T);
+  const uint32_t o0 = col < ncol ? full : kNoColumn, l0 = col < ncol ? last : kNoColumn;
+  const uint32_t o1 = col + 64 < ncol ? full + 64u * sizeof(T) : kNoColumn;
+#pragma unroll
+  for (int i = 0; i < S::NV; ++i) {
+    const int r = c0 + i * S::RPL;
+    const int rc = r < lastg ? r : lastg;
+    const uint32_t so = (uint32_t)(rc * ld) * (uint32_t)sizeof(T);
+    v[0][i] = buf_ld_row<T>(rs, S::RPL > 1 && r >= lastg ? l0 : o0, so);
+    if constexpr (S::SL == 2) v[1][i] = buf_ld_row<T>(rs, o1, so);
+  }
+}
+
+__device__ __forceinline__ double mk_double(unsigned lo, unsigned hi) {
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <int CTRL, int BANK>
+__device__ __forceinline__ double dpp_into(double old, double x) {
+  const uint64_t o = __builtin_bit_cast(uint64_t, old), v = __builtin_bit_cast(uint64_t, x);
+  const int lo = __builtin_amdgcn_update_dpp((int)(unsigned)o, (int)(unsigned)v, CTRL, 0xF, BANK, false);
+  const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(o >> 32), (int)(unsigned)(v >> 32), CTRL, 0xF, BANK, false);
+  return mk_double((unsigned)lo, (unsigned)hi);
+}
+__device__ __forceinline__ unsigned opaque_u(unsigned x) {
+  unsigned y = x;
+  asm volatile("" : "+v"(y));
+  return y;
+}
+// x, which with FRESH the compiler cannot identify with x: a chunk is then converted to double anew
+// for its second use, else the converted values (twice the registers) are kept from the first.  Kept
+// they cost registers up to the two waves per SIMD that pass 1's grid fills, and save conversions:
+// n = 3, 91 columns, 50,000 blocks 54.0 us kept, 57.2 fresh; from n = 6 on they would leave one wave.
+template <bool FRESH, typename T>
+__device__ __forceinline__ T second_use(T x) {
+  if constexpr (FRESH) asm("" : "+v"(x));
+  return x;
+}
+// Fold step ST (lanes l and l ^ 32, 16, 15, 7, 2, 1): lanes with the step's bit clear (5, 4, 3, 2,
+// 1, 0) return a's sum over the pair, the others b's.
+template <int ST>
+__device__ __forceinline__ double fold2(double a, double b, int lane) {
+  const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);
+  if constexpr (ST == 0) {
+    auto x = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
+    auto y = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+    return mk_double(x[0], y[0]) + mk_double(x[1], y[1]);
+  } else if constexpr (ST == 1) {
+    auto x = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
+    auto y = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+    return mk_double(x[0], y[0]) + mk_double(x[1], y[1]);
+  } else if constexpr (ST == 2 || ST == 3) {
+    constexpr int ctrl = ST == 2 ? 0x140 : 0x141;   // row_mirror, row_half_mirror
+    constexpr int hi = ST == 2 ? 0xC : 0xA;         // banks with bit 3 (bit 2) of the lane set
+    const double t = dpp_into<ctrl, hi>(dpp_into<ctrl, 0xF ^ hi>(a, a), b);
+    const double k = dpp_into<0xE4, hi>(a, b);      // quad_perm identity
+    return k + t;
+  } else {
+    constexpr int ctrl = ST == 4 ? 0x4E : 0xB1;     // quad_perm xor 2, xor 1
+    const bool up = lane & (ST == 4 ? 2 : 1);
+    const double send = up ? a : b, k = up ? b : a;
+    return k + dpp_into<ctrl, 0xF>(send, send);
+  }
+}
+template <int ST>
+__device__ __forceinline__ double fold1(double a) {
+  if constexpr (ST <= 1) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, a);
+    return fold2<ST>(a, mk_double(opaque_u((unsigned)u), opaque_u((unsigned)(u >> 32))), 0);
+  } else {
+    constexpr int ctrl = ST == 2 ? 0x140 : (ST == 3 ? 0x141 : (ST == 4 ? 0x4E : 0xB1));
+    return a + dpp_into<ctrl, 0xF>(a, a);
+  }
+}
+template <int ST, int M, int NV>
+__device__ __forceinline__ void fold_steps(double (&s)[NV], int lane) {
+  if constexpr (ST <= 5) {
+    if constexpr (M > 1) {
+#pragma unroll
+      for (int i = 0; i < M / 2; ++i) s[i] = fold2<ST>(s[i], s[i + M / 2], lane);
+      fold_steps<ST + 1, M / 2, NV>(s, lane);
+    } else {
+      s[0] = fold1<ST>(s[0]);
+      fold_steps<ST + 1, 1, NV>(s, lane);
+    }
+  }
+}
+// Sum of row RowStream::sum_row(lane) of a chunk over its columns, w0 / w1 the lane's columns'
+// factors.
+template <typename T, int CW>
+__device__ __forceinline__ double stream_dot(const StreamChunk<T, CW>& v, double w0,
+                                             double w1, int lane) {
+  using S = RowStream<T, CW>;
+  double s[S::NV];
+#pragma unroll
+  for (int i = 0; i < S::NV; ++i) {
+    s[i] = (double)v[0][i] * w0;
+    if constexpr (S::SL == 2) s[i] += (double)v[1][i] * w1;
+  }
+  fold_steps<S::LN == 64 ? 0 : (S::LN == 32 ? 1 : 2), S::NV, S::NV>(s, lane);
+  return s[0];
+}
+
+// f(CW) for ncol columns
+template <typename F>
+__device__ __forceinline__ void stream_width(int ncol, F&& f) {
+  if (ncol <= 16)
+    f(std::integral_constant<int, 16>{});
+  else if (ncol <= 32)
+    f(std::integral_constant<int, 32>{});
+  else if (ncol <= 64)
+    f(std::integral_constant<int, 64>{});
+  else
+    f(std::integral_constant<int, 128>{});
+}
+
 // ---------------------------------------------------------------------------------
-// Blocks, pack-wise: x_i (= | +=) R_i^{-1} (base_i - S_i v) for the blocks of a pack (the
-// packs and workgroup-to-problem map of refinement pass 1); v is the dense-part vector of
-// the pack's problem.  The pack's coupling rows S|c are contiguous: they are streamed 16
-// rows at a time through the wave's LDS tile (column-major, stride 17) and each row's dot
-// with v is summed by four lanes; then lane k back-substitutes block k of the pack.
-//   MODE 0 back-substitution: base_i = c_i (column nB of S|c, staged with weight -1),
+// Blocks: x_i (= | +=) R_i^{-1} (base_i - S_i v) for all blocks, v the dense-part vector of the
+// block's problem.  A wave takes whole units of at most 64 / N consecutive blocks (at most 64
+// coupling rows S|c, contiguous), fewer where the problem has too few blocks for its waves; the rows
+// are streamed with the next chunk in flight, each row's dot with v is left in LDS, then lane k
+// back-substitutes block k of the unit.
+//   MODE 0 back-substitution: base_i = c_i (column nB of S|c, streamed with weight -1),
 //                             v = p_B, p_i set, pivot and finiteness status;
 //   MODE 1 refinement:        base_i = y_i, v = delta_B, p_i incremented;
 //   MODE 2 adjoint:           base_i = y_i, v = u_B, u_i set;
 //   MODE 3 back-substitution for a given c (laid out like p, in ybase): base_i = c_i,
 //                             v = p_B, p_i set, pivot and finiteness status.
 // ---------------------------------------------------------------------------------
-template <typename T, int N, int MODE>
-__global__ void __launch_bounds__(256)
-k_blocks_solve_n(const ProbDesc* __restrict__ probs, const int32_t* __restrict__ wg_prob,
-                 const int64_t* __restrict__ pack_blk, const T* __restrict__ Rblk, const T* __restrict__ Sc,
-                 const double* __restrict__ vbuf, const double* __restrict__ ybase, double* __restrict__ x,
-                 int* __restrict__ status) {
-  constexpr int CH = 16, LS = CH + 1;
-  constexpr int MAXR = 64 * N;  // coupling rows of a pack (at most 64 blocks)
-  __shared__ T tile_all[4][kMaxDense * LS];
-  __shared__ double rhs_all[4][MAXR + CH];
-  const int lane = threadIdx.x & 63;
-  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  T* tile = tile_all[wv];
-  double* rhs = rhs_all[wv];
-  const int pi = wg_prob[blockIdx.x];
-  const ProbDesc& P = probs[pi];
+template <typename T, int N, int MODE, int CW>
+__device__ __forceinline__ void blocks_solve_units(const ProbDesc& P, int pi, const T* __restrict__ Rblk,
+                                                   const T* __restrict__ Sc, const double* __restrict__ v,
+                                                   const double* __restrict__ ybase, double* __restrict__ x,
+                                                   int* __restrict__ status, double* rhs, int wv, int lane) {
+  using S = RowStream<T, CW>;
   const int nB = P.nB, L = P.L;
-  const int64_t koff = P.koff, noff = P.noff, soff = P.soff;
-  const double* v = MODE == 1 ? vbuf + (int64_t)pi * kMaxDense : vbuf + P.noff + P.K * N;
-  // staged columns: nB (and the c column with weight -1 in mode 0)
+  const int64_t koff = P.koff, noff = P.noff, soff = P.soff, K = P.K;
   const int ncol = MODE == 0 ? L : nB;
-  const int qi = lane & 15, qq = lane >> 4;
-  double pq[kMaxDense / 4];
-#pragma unroll
-  for (int t = 0; t < kMaxDense / 4; ++t) {
-    const int j = 4 * t + qq;
-    pq[t] = j < nB ? v[j] : ((MODE == 0 && j == nB) ? -1.0 : 0.0);
+  const int col = lane & (S::LN - 1);
+  double w0 = v[col < nB ? col : 0], w1 = 0.0;
+  if (col >= nB) w0 = MODE == 0 && col == nB ? -1.0 : 0.0;
+  if constexpr (S::SL == 2) {
+    w1 = v[col + 64 < nB ? col + 64 : 0];
+    if (col + 64 >= nB) w1 = MODE == 0 && col + 64 == nB ? -1.0 : 0.0;
   }
-  const bool c0ok = lane < ncol, c1ok = lane + 64 < ncol;
-  const uint32_t co0 = (uint32_t)(c0ok ? lane : 0) * (uint32_t)sizeof(T);
-  const uint32_t co1 = (uint32_t)(c1ok ? lane + 64 : 0) * (uint32_t)sizeof(T);
-  const int64_t lw = blockIdx.x - P.wg0;
-  const int64_t pend = P.pack0 + P.npacks;
-  for (int64_t pk = P.pack0 + lw * 4 + wv; pk < pend; pk += (int64_t)P.nwg * 4) {
-    const int64_t b0 = pack_blk[pk];
-    const int nb = (int)(pack_blk[pk + 1] - b0);
-    const int rs = nb * N;
-    // this lane's block (lanes < nb): R_i and the base values, loaded before the stream
-    const int kb = lane < nb ? lane : nb - 1;
-    const int64_t blk = b0 + kb;
-    const int64_t lb = blk - koff;
+  const int64_t waves = (int64_t)P.nwg * 4;
+  const int64_t even = (K + waves - 1) / waves;  // blocks of a wave
+  constexpr int UMIN = 16 / N > 0 ? 16 / N : 1, UMAX = 64 / N;
+  const int unit = even < UMIN ? UMIN : (even > UMAX ? UMAX : (int)even);
+  for (int64_t lb0 = ((blockIdx.x - P.wg0) * 4 + wv) * (int64_t)unit; lb0 < K; lb0 += waves * unit) {
+    const int nb = K - lb0 < unit ? (int)(K - lb0) : unit;
+    const int rows = nb * N;
+    const __amdgpu_buffer_rsrc_t rsS =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(Sc + soff + lb0 * N * L), 0, 0x7fffffff, 0x00020000);
+    StreamChunk<T, CW> va, vb;
+    stream_load<T, CW>(va, rsS, 0, rows, L, ncol, lane);
+    // this lane's block (lanes < nb): R_i and the base values
+    const int64_t lb = lb0 + (lane < nb ? lane : nb - 1), blk = koff + lb;
     T Rb[N * N];
 #pragma unroll
     for (int e = 0; e < N * N; ++e) Rb[e] = Rblk[blk * (N * N) + e];
-    double base[N];
+    double base[N], xold[N];
 #pragma unroll
-    for (int c = 0; c < N; ++c) base[c] = MODE == 0 ? 0.0 : (MODE == 3 ? ybase[noff + lb * N + c] : ybase[blk * N + c]);
-    double xold[N];
-#pragma unroll
-    for (int c = 0; c < N; ++c) xold[c] = MODE == 1 ? x[noff + lb * N + c] : 0.0;
-    const __amdgpu_buffer_rsrc_t rsS =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(Sc + soff + (b0 - koff) * N * L), 0, 0x7fffffff,
-                                          0x00020000);
-    for (int c0 = 0; c0 < rs; c0 += CH) {
-      const int last = rs - 1 - c0;
-      T v0[CH], v1[CH];
-#pragma unroll
-      for (int i = 0; i < CH; ++i) {
-        const int ri = i < last ? i : last;
-        const uint32_t so = (uint32_t)((c0 + ri) * L) * (uint32_t)sizeof(T);
-        const T x0 = buf_ld_row<T>(rsS, co0, so);
-        const T x1 = buf_ld_row<T>(rsS, co1, so);
-        v0[i] = c0ok ? x0 : T(0);
-        v1[i] = c1ok ? x1 : T(0);
-      }
-#pragma unroll
-      for (int i = 0; i < CH; ++i) {
-        tile[lane * LS + i] = v0[i];
-        tile[(lane + 64) * LS + i] = v1[i];
-      }
-      wave_lds_sync();
-      double acc = 0.0;
-      auto tier = [&](auto t_begin) {
-        constexpr int tb = decltype(t_begin)::value;
-#pragma unroll
-        for (int t = tb; t < tb + 8; ++t) acc += (double)tile[(4 * t + qq) * LS + qi] * pq[t];
-      };
-      tier(std::integral_constant<int, 0>{});
-      if (ncol > 32) tier(std::integral_constant<int, 8>{});
-      if (ncol > 64) tier(std::integral_constant<int, 16>{});
-      if (ncol > 96) tier(std::integral_constant<int, 24>{});
-      acc += __shfl_xor(acc, 16, 64);
-      acc += __shfl_xor(acc, 32, 64);
-      if (qq == 0) rhs[c0 + qi] = -acc;  // -(S v) (mode 0: c - S p_B)
-      wave_lds_sync();  // the next chunk overwrites the tile
+    for (int c = 0; c < N; ++c) {
+      base[c] = MODE == 0 ? 0.0 : (MODE == 3 ? ybase[noff + lb * N + c] : ybase[blk * N + c]);
+      xold[c] = MODE == 1 ? x[noff + lb * N + c] : 0.0;
     }
+    auto dots = [&](const StreamChunk<T, CW>& vv, int c0) {
+      rhs[c0 + S::sum_row(lane)] = -stream_dot<T, CW>(vv, w0, w1, lane);  // -(S v) (mode 0: c - S p_B)
+    };
+    for (int c0 = 0;;) {
+      if (c0 + S::CHR < rows) stream_load<T, CW>(vb, rsS, c0 + S::CHR, rows, L, ncol, lane);
+      dots(va, c0);
+      if ((c0 += S::CHR) >= rows) break;
+      if (c0 + S::CHR < rows) stream_load<T, CW>(va, rsS, c0 + S::CHR, rows, L, ncol, lane);
+      dots(vb, c0);
+      if ((c0 += S::CHR) >= rows) break;
+    }
+    wave_lds_sync();
     if (lane < nb) {
-      double rr[N], out[N];
-#pragma unroll
-      for (int c = 0; c < N; ++c) rr[c] = base[c] + rhs[lane * N + c];
+      double out[N];
 #pragma unroll
       for (int i = N - 1; i >= 0; --i) {
-        double sacc = rr[i];
+        double sacc = base[i] + rhs[lane * N + i];
 #pragma unroll
         for (int j = i + 1; j < N; ++j) sacc -= (double)Rb[i * N + j] * out[j];
         out[i] = sacc / (double)Rb[i * N + i];
@@ -387,8 +507,26 @@ k_blocks_solve_n(const ProbDesc* __restrict__ probs, const int32_t* __restrict__
         if (nonfinite) set_status(status + pi, ST_NONFINITE);
       }
     }
-    wave_lds_sync();  // the next pack overwrites rhs
+    wave_lds_sync();  // the next unit overwrites rhs
   }
+}
+
+template <typename T, int N, int MODE>
+__global__ void __launch_bounds__(256)
+k_blocks_solve_n(const ProbDesc* __restrict__ probs, const int32_t* __restrict__ wg_prob,
+                 const T* __restrict__ Rblk, const T* __restrict__ Sc,
+                 const double* __restrict__ vbuf, const double* __restrict__ ybase, double* __restrict__ x,
+                 int* __restrict__ status) {
+  __shared__ double rhs_all[4][128];  // a unit's rows, rounded up to whole chunks
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int pi = wg_prob[blockIdx.x];
+  const ProbDesc& P = probs[pi];
+  // with nB == 0 the dense vector may be empty: any element stands in (weight 0)
+  const double* v = MODE == 1 ? vbuf + (int64_t)pi * kMaxDense : vbuf + P.noff + (P.nB > 0 ? P.K * N : 0);
+  stream_width(MODE == 0 ? P.L : P.nB, [&](auto C) {
+    blocks_solve_units<T, N, MODE, decltype(C)::value>(P, pi, Rblk, Sc, v, ybase, x, status, rhs_all[wv], wv, lane);
+  });
 }
 
 template <typename T, int MODE>
@@ -399,7 +537,7 @@ static hipError_t launch_blocks_solve(const BatchView& bv, const T* Rblk, const 
 #define QRK_BS(NN)                                                                                          \
   case NN:                                                                                                  \
     hipLaunchKernelGGL((k_blocks_solve_n<T, NN, MODE>), dim3(bv.nwg), dim3(256), 0, st, bv.probs, bv.wg_prob, \
-                       bv.pack_blk, Rblk, Sc, vbuf, ybase, x, status);                                     \
+                       Rblk, Sc, vbuf, ybase, x, status);                                                  \
     break;
     QRK_BS(1) QRK_BS(2) QRK_BS(3) QRK_BS(4) QRK_BS(5) QRK_BS(6) QRK_BS(7) QRK_BS(8)
 #undef QRK_BS
@@ -432,17 +570,199 @@ hipError_t launch_adjoint_blocks(const BatchView& bv, const T* Rblk, const T* Sc
 // Refinement pass 1: one wave per pack of whole blocks (at most 64 rows).
 //   r = b - A_i p_i - B p_B;  g_i = A_i^T r - lam d_i^2 p_i;  y_i = R_i^{-T} g_i;
 //   per-workgroup partial of  B^T r - sum_i S_i^T y_i.
-// The pack's rows of B are read once, coalesced, 16 rows at a time, and staged in the wave's
-// LDS tile column-major with an odd column stride (17), so both products read it without
-// bank conflicts: B p_B with four lanes per row (each summing every fourth column, then two
-// shuffles), B^T r with one lane per column straight from the registers the chunk was
-// loaded into.  Every sum runs in a fixed order, so the partials are deterministic.
+// b - A_i p_i and A_i's products with r go with a lane per row of the pack, A_i^T r with a lane per
+// (block, unknown), the triangular solves with a lane per block.  The pack's rows of B are streamed
+// once (RowStream), the next chunk in flight while one is worked on: B p_B by folding, B^T r from
+// the same registers with a lane per column.  Every sum runs in a fixed order, so the partials are
+// deterministic.
 // Workgroup w serves problem wg_prob[w] only; its packs are that problem's packs
 // lw*4 + wave, lw*4 + wave + 4*nwg, ... (lw = w - wg0), its partial goes to part[w].
 // CAM: the coupled columns are cameras of ldb columns (nB = ncam * ldb); B holds each row's ldb
-// values and cam[row] its camera (outside [0, ncam): none), so a staged row is zero outside its
+// values and cam[row] its camera (outside [0, ncam): none), so a streamed row is zero outside its
 // camera's columns.
 // ---------------------------------------------------------------------------------
+template <int N>
+struct Pass1Lds {
+  double pg[64 * N + 64];  // p_i of the pack's blocks, then A_i^T r, then y (0 past the last block)
+  double prod[64 * N];     // A_row * r per pack row
+  double base[64];         // b - A_i p_i
+  double rr[64];           // r
+  int lo[65];              // first row of every block of the pack
+};
+
+template <typename T, int N, bool CAM, int CW>
+__device__ __forceinline__ void pass1_packs(const ProbDesc& P, const int64_t* __restrict__ pack_blk,
+                                            const int64_t* __restrict__ row_off, const T* __restrict__ A,
+                                            const T* __restrict__ B, const int32_t* __restrict__ cam,
+                                            const T* __restrict__ bvec, const double* __restrict__ d, double lam,
+                                            const T* __restrict__ Rblk, const T* __restrict__ Sc,
+                                            const double* __restrict__ p, double* __restrict__ y, Pass1Lds<N>& lds,
+                                            int wv, int lane, double& t0, double& t1) {
+  using S = RowStream<T, CW>;
+  const int nB = P.nB, L = P.L;
+  const int64_t koff = P.koff, noff = P.noff, moff = P.moff, soff = P.soff;
+  const int ldb = nB > 0 ? (int)P.ldb : 0;
+  const uint32_t ncam = CAM ? (uint32_t)(nB / ldb) : 0u;
+  const int g = lane / S::LN, col = lane & (S::LN - 1);
+  const double* pBv = p + noff + (nB > 0 ? P.K * N : 0);
+  double w0 = pBv[col < nB ? col : 0], w1 = 0.0;
+  if (col >= nB) w0 = 0.0;
+  if constexpr (S::SL == 2) {
+    w1 = pBv[col + 64 < nB ? col + 64 : 0];
+    if (col + 64 >= nB) w1 = 0.0;
+  }
+  const int64_t lw = blockIdx.x - P.wg0;
+  const int64_t pend = P.pack0 + P.npacks;
+  for (int64_t pk = P.pack0 + lw * 4 + wv; pk < pend; pk += (int64_t)P.nwg * 4) {
+    const int64_t b0 = pack_blk[pk];
+    const int nb = (int)(pack_blk[pk + 1] - b0);
+    const int64_t pr0 = row_off[b0];
+    const int prows = (int)(row_off[b0 + nb] - pr0);
+    // with nB == 0 there may be no B at all: every column is out of range then, nothing is read
+    const T* Bbase = nB > 0 ? B + P.boff + (pr0 - moff) * ldb : bvec + pr0;
+    const __amdgpu_buffer_rsrc_t rsB =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(Bbase), 0, 0x7fffffff, 0x00020000);
+    const int64_t grow = pr0 + (lane < prows ? lane : prows - 1);  // this lane's row (if prows > 0)
+    int camv = 0;
+    auto load = [&](StreamChunk<T, CW>& v, int c0) {
+      if constexpr (CAM) {
+        static_assert(S::RPL == 1, "a camera row takes the whole wave");
+#pragma unroll
+        for (int i = 0; i < S::NV; ++i) {
+          const int row = c0 + i < prows ? c0 + i : prows - 1;
+          const int cr = __builtin_amdgcn_readlane(camv, row);
+          const int cb = (uint32_t)cr < ncam ? cr * ldb : 1 << 20;
+          const uint32_t k0 = (uint32_t)(lane - cb), k1 = (uint32_t)(lane + 64 - cb);
+          const uint32_t so = (uint32_t)(row * ldb) * (uint32_t)sizeof(T);
+          v[0][i] = buf_ld_row<T>(rsB, k0 < (uint32_t)ldb ? k0 * (uint32_t)sizeof(T) : kNoColumn, so);
+          if constexpr (S::SL == 2)
+            v[1][i] = buf_ld_row<T>(rsB, k1 < (uint32_t)ldb ? k1 * (uint32_t)sizeof(T) : kNoColumn, so);
+        }
+      } else {
+        stream_load<T, CW>(v, rsB, c0, prows, ldb, nB, lane);
+      }
+    };
+    StreamChunk<T, CW> va, vb;
+    T arow[N] = {}, bval = T(0);
+    if (prows > 0) {  // a pack of blocks without rows has none to read
+      if constexpr (CAM) camv = cam[grow];
+      load(va, 0);
+#pragma unroll
+      for (int c = 0; c < N; ++c) arow[c] = A[grow * N + c];
+      bval = bvec[grow];
+    }
+    // this lane's block (lanes < nb)
+    const int64_t blk = b0 + (lane < nb ? lane : nb - 1);
+    const int64_t lb = blk - koff;
+    const int lo = (int)(row_off[blk] - pr0);
+    double dd[N], pp[N];
+    T Rb[N * N];
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+      dd[c] = d[noff + lb * N + c];
+      pp[c] = p[noff + lb * N + c];
+    }
+#pragma unroll
+    for (int e = 0; e < N * N; ++e) Rb[e] = Rblk[blk * (N * N) + e];
+    if (lane < nb) {
+#pragma unroll
+      for (int c = 0; c < N; ++c) lds.pg[lane * N + c] = pp[c];
+      lds.lo[lane] = lo;
+    }
+    if (lane == 0) lds.lo[nb] = prows;
+    int rb = 0;  // the block of this lane's row: the last one that starts at or before it
+    for (int k = 1; k < nb; ++k) rb += lane >= __builtin_amdgcn_readlane(lo, k) ? 1 : 0;
+    if (lane >= prows) rb = nb - 1;
+    wave_lds_sync();
+    {
+      double dot = 0.0;
+#pragma unroll
+      for (int c = 0; c < N; ++c) dot += (double)arow[c] * lds.pg[rb * N + c];
+      lds.base[lane] = (double)bval - dot;
+    }
+    wave_lds_sync();
+    auto work = [&](const StreamChunk<T, CW>& v, int c0) {
+      const double acc = stream_dot<T, CW>(v, w0, w1, lane);
+      const int row = c0 + S::sum_row(lane);  // < 64: a chunk does not pass the pack's 64 rows
+      const double bs = lds.base[row];
+      lds.rr[row] = row < prows ? bs - acc : 0.0;
+      wave_lds_sync();
+#pragma unroll
+      for (int i = 0; i < S::NV; ++i) {
+        const double rv = lds.rr[c0 + i * S::RPL + g];
+        t0 += (double)second_use<(N > 5)>(v[0][i]) * rv;
+        if constexpr (S::SL == 2) t1 += (double)second_use<(N > 5)>(v[1][i]) * rv;
+      }
+    };
+    for (int c0 = 0; c0 < prows;) {
+      if (c0 + S::CHR < prows) load(vb, c0 + S::CHR);
+      work(va, c0);
+      if ((c0 += S::CHR) >= prows) break;
+      if (c0 + S::CHR < prows) load(va, c0 + S::CHR);
+      work(vb, c0);
+      c0 += S::CHR;
+    }
+    // the coupling rows of the pack are contiguous: their first chunk travels during the solves
+    const int rs = nb * N;
+    const __amdgpu_buffer_rsrc_t rsS = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<T*>(Sc + soff + (b0 - koff) * N * L), 0, 0x7fffffff, 0x00020000);
+    stream_load<T, CW>(va, rsS, 0, rs, L, nB, lane);
+    if (lane < prows) {
+      const double rv = lds.rr[lane];
+#pragma unroll
+      for (int c = 0; c < N; ++c) lds.prod[lane * N + c] = (double)arow[c] * rv;
+    }
+    wave_lds_sync();
+    for (int e = lane; e < rs; e += 64) {  // (A_i^T r)_c, rows in order, eight reads in flight
+      const int k = e / N, c = e - k * N;
+      const int r1 = lds.lo[k + 1];
+      double sum = 0.0;
+      for (int r = lds.lo[k]; r < r1; r += 8) {
+        double q[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) q[u] = lds.prod[(r + u < r1 ? r + u : r1 - 1) * N + c];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum += r + u < r1 ? q[u] : 0.0;
+      }
+      lds.pg[e] = sum;
+    }
+    wave_lds_sync();
+    if (lane < nb) {  // R_i^T y = A_i^T r - lam d_i^2 p_i (R_i upper triangular, row-major)
+      double yy[N];
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        double sacc = lds.pg[lane * N + i] - lam * dd[i] * dd[i] * pp[i];
+#pragma unroll
+        for (int j = 0; j < i; ++j) sacc -= (double)Rb[j * N + i] * yy[j];
+        yy[i] = sacc / (double)Rb[i * N + i];
+      }
+#pragma unroll
+      for (int c = 0; c < N; ++c) {
+        y[blk * N + c] = yy[c];
+        lds.pg[lane * N + c] = yy[c];
+      }
+    }
+    lds.pg[rs + lane] = 0.0;
+    wave_lds_sync();
+    auto coupling = [&](const StreamChunk<T, CW>& v, int s0) {
+#pragma unroll
+      for (int i = 0; i < S::NV; ++i) {
+        const double yc = lds.pg[s0 + i * S::RPL + g];
+        t0 -= (double)v[0][i] * yc;
+        if constexpr (S::SL == 2) t1 -= (double)v[1][i] * yc;
+      }
+    };
+    for (int s0 = 0;;) {
+      if (s0 + S::CHR < rs) stream_load<T, CW>(vb, rsS, s0 + S::CHR, rs, L, nB, lane);
+      coupling(va, s0);
+      if ((s0 += S::CHR) >= rs) break;
+      if (s0 + S::CHR < rs) stream_load<T, CW>(va, rsS, s0 + S::CHR, rs, L, nB, lane);
+      coupling(vb, s0);
+      if ((s0 += S::CHR) >= rs) break;
+    }
+    wave_lds_sync();  // the next pack overwrites the wave's LDS
+  }
+}
 
 template <typename T, int N, bool CAM>
 __global__ void __launch_bounds__(256)
@@ -453,222 +773,31 @@ k_refine_pass1(const ProbDesc* __restrict__ probs, const int32_t* __restrict__ w
                const double* __restrict__ d, const double* __restrict__ lamv, const T* __restrict__ Rblk,
                const T* __restrict__ Sc, const double* __restrict__ p, double* __restrict__ y,
                double* __restrict__ part) {
-  constexpr int CH = 16;      // rows per staged chunk
-  constexpr int LS = CH + 1;  // column stride of the staged tile
-  static_assert(4 * kMaxDense * LS * sizeof(T) >= 4 * kMaxDense * sizeof(double), "reduction fits the tile");
-  __shared__ T tile_all[4][kMaxDense * LS];
-  __shared__ double rr_all[4][64 + CH];         // r per pack row (0 past the pack)
-  __shared__ double prod_all[4][64 * N];        // A_row * r per pack row
-  __shared__ double yv_all[4][64 * N + CH];     // y per coupling row (0 past the pack's blocks)
-  __shared__ int rowblk_all[4][64];
+  __shared__ Pass1Lds<N> lds_all[4];
+  __shared__ double red[4][kMaxDense];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  T* tile = tile_all[wv];
-  double* rr = rr_all[wv];
-  double* prod = prod_all[wv];
-  double* yv = yv_all[wv];
-  int* rowblk = rowblk_all[wv];
   const int pi = wg_prob[blockIdx.x];
   const ProbDesc& P = probs[pi];
-  const int nB = P.nB, L = P.L;
-  const int64_t koff = P.koff, noff = P.noff, moff = P.moff, soff = P.soff;
-  const int ldb = nB > 0 ? (int)P.ldb : 0;
-  const uint32_t ncam = CAM ? (uint32_t)(nB / ldb) : 0u;
+  const int nB = P.nB;
   const double lam = lamv[pi];
-  const double* pBv = p + noff + P.K * N;
-  const int qi = lane & 15, qq = lane >> 4;  // row pass: row qi of the chunk, columns 4t + qq
-  double pq[kMaxDense / 4];
-#pragma unroll
-  for (int t = 0; t < kMaxDense / 4; ++t) {
-    const int j = 4 * t + qq;
-    pq[t] = j < nB ? pBv[j] : 0.0;
-  }
-  const bool c0ok = lane < nB, c1ok = lane + 64 < nB;
-  const uint32_t co0 = (uint32_t)(c0ok ? lane : 0) * (uint32_t)sizeof(T);
-  const uint32_t co1 = (uint32_t)(c1ok ? lane + 64 : 0) * (uint32_t)sizeof(T);
-  double t0 = 0.0, t1 = 0.0;  // partial B^T r - S^T y for columns lane, lane + 64
-  const int64_t lw = blockIdx.x - P.wg0;
-  const int64_t pend = P.pack0 + P.npacks;
-  for (int64_t pk = P.pack0 + lw * 4 + wv; pk < pend; pk += (int64_t)P.nwg * 4) {
-    const int64_t b0 = pack_blk[pk];
-    const int nb = (int)(pack_blk[pk + 1] - b0);
-    const int64_t pr0 = row_off[b0];
-    const int prows = (int)(row_off[b0 + nb] - pr0);
-    if (lane < nb) {
-      const int lo = (int)(row_off[b0 + lane] - pr0), hi = (int)(row_off[b0 + lane + 1] - pr0);
-      for (int r = lo; r < hi; ++r) rowblk[r] = lane;
-    }
-    wave_lds_sync();
-    // with nB == 0 there may be no B at all: the (discarded) loads then read b[pr0]
-    const T* Bbase = nB > 0 ? B + P.boff + (pr0 - moff) * ldb : bvec + pr0;
-    const __amdgpu_buffer_rsrc_t rsB =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(Bbase), 0, 0x7fffffff, 0x00020000);
-    // the pack's rows in chunks; W: the problem has coupled columns past 64 (the second column
-    // slot of each lane holds some), else that slot is left out of the loads and products
-    auto chunks = [&](auto Wc) {
-      constexpr bool W = decltype(Wc)::value;
-      for (int c0 = 0; c0 < prows; c0 += CH) {
-        const int last = prows - 1 - c0;  // rows past the pack re-read its last row; their r is 0
-        // this lane's row of the chunk for the r update (lanes 0..15): its A row and p_i
-        const int myrow = c0 + (qi < last ? qi : last);
-        const int64_t grow = pr0 + myrow;
-        const int64_t lbr = b0 - koff + rowblk[myrow];
-        T arow[N];
-        double prow[N];
-#pragma unroll
-        for (int c = 0; c < N; ++c) {
-          arow[c] = A[grow * N + c];
-          prow[c] = p[noff + lbr * N + c];
-        }
-        const T bval = bvec[grow];
-        // stage rows c0 .. c0 + 15; columns >= nB are zeros
-        T v0[CH], v1[W ? CH : 1];
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-          const int ri = i < last ? i : last;
-          const uint32_t so = (uint32_t)((c0 + ri) * ldb) * (uint32_t)sizeof(T);
-          if constexpr (CAM) {
-            const int cr = cam[pr0 + c0 + ri];
-            const bool seen = (uint32_t)cr < ncam;
-            const int cb = (seen ? cr : 0) * ldb;
-            const uint32_t k0 = (uint32_t)(lane - cb), k1 = (uint32_t)(lane + 64 - cb);
-            const bool on0 = seen && k0 < (uint32_t)ldb, on1 = seen && k1 < (uint32_t)ldb;
-            const T x0 = buf_ld_row<T>(rsB, (on0 ? k0 : 0u) * (uint32_t)sizeof(T), so);
-            v0[i] = on0 ? x0 : T(0);
-            if constexpr (W) {
-              const T x1 = buf_ld_row<T>(rsB, (on1 ? k1 : 0u) * (uint32_t)sizeof(T), so);
-              v1[i] = on1 ? x1 : T(0);
-            }
-          } else {
-            const T x0 = buf_ld_row<T>(rsB, co0, so);
-            v0[i] = c0ok ? x0 : T(0);
-            if constexpr (W) {
-              const T x1 = buf_ld_row<T>(rsB, co1, so);
-              v1[i] = c1ok ? x1 : T(0);
-            }
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-          tile[lane * LS + i] = v0[i];
-          if constexpr (W) tile[(lane + 64) * LS + i] = v1[i];
-        }
-        wave_lds_sync();
-        // B p_B for row c0 + qi: lanes qi, qi + 16, qi + 32, qi + 48 split the columns
-        // (32-column tiers; the columns past nB are zeros)
-        double acc = 0.0;
-        auto tier = [&](auto t_begin) {
-          constexpr int tb = decltype(t_begin)::value;
-#pragma unroll
-          for (int t = tb; t < tb + 8; ++t) acc += (double)tile[(4 * t + qq) * LS + qi] * pq[t];
-        };
-        tier(std::integral_constant<int, 0>{});
-        if (nB > 32) tier(std::integral_constant<int, 8>{});
-        if constexpr (W) {
-          tier(std::integral_constant<int, 16>{});
-          if (nB > 96) tier(std::integral_constant<int, 24>{});
-        }
-        acc += __shfl_xor(acc, 16, 64);
-        acc += __shfl_xor(acc, 32, 64);
-        if (qq == 0) {
-          double dot = 0.0;
-#pragma unroll
-          for (int c = 0; c < N; ++c) dot += (double)arow[c] * prow[c];
-          const double rv = qi <= last ? (double)bval - dot - acc : 0.0;
-          rr[c0 + qi] = rv;
-          if (qi <= last) {
-#pragma unroll
-            for (int c = 0; c < N; ++c) prod[(c0 + qi) * N + c] = (double)arow[c] * rv;
-          }
-        }
-        wave_lds_sync();
-        // B^T r over the chunk's rows, from the registers the chunk was loaded into
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-          const double rv = rr[c0 + i];
-          t0 += (double)v0[i] * rv;
-          if constexpr (W) t1 += (double)v1[i] * rv;
-        }
-        wave_lds_sync();  // the next chunk overwrites the tile
-      }
-    };
-    if (nB > 64)
-      chunks(std::true_type{});
-    else
-      chunks(std::false_type{});
-    // per block: g_i = A_i^T r - lam d_i^2 p_i, y_i = R_i^{-T} g_i
-    if (lane < nb) {
-      const int64_t blk = b0 + lane;
-      const int64_t lb = blk - koff;
-      double dd[N], pp[N];
-      T Rb[N * N];
-#pragma unroll
-      for (int c = 0; c < N; ++c) {
-        dd[c] = d[noff + lb * N + c];
-        pp[c] = p[noff + lb * N + c];
-      }
-#pragma unroll
-      for (int e = 0; e < N * N; ++e) Rb[e] = Rblk[blk * (N * N) + e];
-      const int lo = (int)(row_off[blk] - pr0), hi = (int)(row_off[blk + 1] - pr0);
-      double g[N];
-#pragma unroll
-      for (int c = 0; c < N; ++c) g[c] = 0.0;
-      for (int r = lo; r < hi; ++r)
-#pragma unroll
-        for (int c = 0; c < N; ++c) g[c] += prod[r * N + c];
-#pragma unroll
-      for (int c = 0; c < N; ++c) g[c] -= lam * dd[c] * dd[c] * pp[c];
-      // R_i^T y = g (R_i upper triangular, row-major)
-      double yy[N];
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        double sacc = g[i];
-#pragma unroll
-        for (int j = 0; j < i; ++j) sacc -= (double)Rb[j * N + i] * yy[j];
-        yy[i] = sacc / (double)Rb[i * N + i];
-      }
-#pragma unroll
-      for (int c = 0; c < N; ++c) {
-        y[blk * N + c] = yy[c];
-        yv[lane * N + c] = yy[c];
-      }
-    }
-    const int rs = nb * N;  // coupling rows of the pack
-    if (lane < CH) yv[rs + lane] = 0.0;
-    wave_lds_sync();
-    // S^T y over the pack's coupling rows (contiguous), 16 rows at a time
-    const __amdgpu_buffer_rsrc_t rsS =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(Sc + soff + (b0 - koff) * N * L), 0, 0x7fffffff,
-                                          0x00020000);
-    const uint32_t so0 = (uint32_t)(c0ok ? lane : 0) * (uint32_t)sizeof(T);
-    const uint32_t so1 = (uint32_t)(c1ok ? lane + 64 : 0) * (uint32_t)sizeof(T);
-    for (int s0 = 0; s0 < rs; s0 += CH) {
-      const int last = rs - 1 - s0;
-      T w0[CH], w1[CH];
-#pragma unroll
-      for (int i = 0; i < CH; ++i) {
-        const int ri = i < last ? i : last;
-        const uint32_t so = (uint32_t)((s0 + ri) * L) * (uint32_t)sizeof(T);
-        w0[i] = buf_ld_row<T>(rsS, so0, so);
-        w1[i] = buf_ld_row<T>(rsS, so1, so);
-      }
-#pragma unroll
-      for (int i = 0; i < CH; ++i) {
-        const double yc = yv[s0 + i];
-        if (c0ok) t0 -= (double)w0[i] * yc;
-        if (c1ok) t1 -= (double)w1[i] * yc;
-      }
-    }
-    wave_lds_sync();
-  }
-  __syncthreads();  // every wave is done with its tile: the tiles hold the reduction now
-  double* red = reinterpret_cast<double*>(&tile_all[0][0]);
-  red[wv * kMaxDense + lane] = t0;
-  red[wv * kMaxDense + lane + 64] = t1;
+  double t0 = 0.0, t1 = 0.0;  // partial B^T r - S^T y of the lane's columns (and rows of a load)
+  int rowstep = 64;           // lanes per row
+  stream_width(CAM && nB <= 32 ? 64 : nB, [&](auto C) {
+    constexpr int CW = CAM && decltype(C)::value < 64 ? 64 : decltype(C)::value;
+    rowstep = RowStream<T, CW>::LN;
+    pass1_packs<T, N, CAM, CW>(P, pack_blk, row_off, A, B, cam, bvec, d, lam, Rblk, Sc, p, y, lds_all[wv], wv, lane,
+                               t0, t1);
+  });
+  red[wv][lane] = t0;
+  red[wv][lane + 64] = t1;
   __syncthreads();
-  for (int j = threadIdx.x; j < nB; j += blockDim.x)
-    part[(int64_t)blockIdx.x * kMaxDense + j] =
-        ((red[j] + red[kMaxDense + j]) + red[2 * kMaxDense + j]) + red[3 * kMaxDense + j];
+  for (int j = threadIdx.x; j < nB; j += blockDim.x) {
+    double sum = 0.0;
+    for (int w = 0; w < 4; ++w)
+      for (int o = j; o < (j < 64 ? 64 : kMaxDense); o += rowstep) sum += red[w][o];
+    part[(int64_t)blockIdx.x * kMaxDense + j] = sum;
+  }
 }
 
 template <typename T>
