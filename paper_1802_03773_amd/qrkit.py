@@ -365,7 +365,9 @@ class BlockAngularSolver(Factor):
         if "dA" in want:
             out["dA"] = torch.empty((self.M, self.n), dtype=td, device="cuda")
         if "dB" in want and self.nB > 0:
-            out["dB"] = torch.zeros((self.M, self.ldb), dtype=td, device="cuda")
+            # every column is written; only the padding of a wider row stride needs the zeros
+            new = torch.empty if self.ldb == self.nB else torch.zeros
+            out["dB"] = new((self.M, self.ldb), dtype=td, device="cuda")
         if "db" in want:
             out["db"] = torch.empty(self.M, dtype=td, device="cuda")
         if "dlam" in want:

@@ -42,3 +42,24 @@ def test_block_heights(heights, nB):
     p, st = gpu_solve_blockangular(inst, sweeps=2)
     assert st[0] == 0, st
     assert p_err(p, p_ref, inst.d) <= 1e-10
+
+
+@pytest.mark.parametrize("n,nB", [(1, 16), (3, 30), (3, 90), (5, 64), (8, 127)])
+@pytest.mark.parametrize("heights", [[0, 9], [0, 0, 0, 20], [12], [56, 0, 8]])
+def test_adjoint_rows(heights, n, nB):
+    """The adjoint's streams in float64 on the same heights; 1e-9 as in the other adjoint tests."""
+    import torch
+    from oracle import adjoint
+    from tests.gpu_util import rel_err
+    K = 150
+    inst = gen.make_blockangular(30 + nB, K=K, m=np.resize(heights, K), n=n, nB=nB, lam=1.0, dtype=np.float64)
+    inst.d = np.ones_like(inst.d)
+    p_ref, f = refine.reference_solution(inst)
+    log(f"adjoint streams heights={heights} n={n} nB={nB}")
+    p, st, solver, _ = gpu_solve_blockangular(inst, sweeps=1, return_solver=True)
+    assert st[0] == 0, st
+    g = np.cos(np.arange(inst.N))
+    ref = adjoint.adjoint_blockangular(inst, f, p_ref, g)
+    out = solver.solve_adjoint(torch.from_numpy(p).cuda(), torch.from_numpy(g).cuda())
+    for k in ("dA", "dB", "db", "dd", "dlam"):
+        assert rel_err(np.ravel(out[k].cpu().numpy()), np.ravel(ref[k])) <= 1e-9, k
