@@ -129,26 +129,33 @@ k_band_first_row(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__
   for (int64_t c = c0; c <= c1; ++c) f[c] = (int32_t)i;
 }
 
-// g = J^T r - lam d^2 v (float64), one thread per column: column j of a problem collects the
-// rows whose start lies in [j - w + 1, j] in row order, so the sum is deterministic.  The row
-// ranges come from the first-row table.  A workgroup covers 256 consecutive columns of one
-// problem: the starts, residuals and values of its rows (one contiguous range) are copied to
-// LDS with coalesced loads, eight per thread in flight, and each column then reads only LDS.
-// Ranges beyond the LDS capacity read their rows from memory.
+// g = J^T r - lam d^2 v (float64), two threads per column: column j of a problem collects the
+// rows whose start lies in [j - w + 1, j], one thread every other row of the range in order, and
+// the two sums are added, so the result is deterministic.  The row ranges come from the
+// first-row table.  A workgroup covers 128 consecutive columns of one problem: the starts,
+// residuals and values of its rows (one contiguous range) are copied to LDS with coalesced
+// loads, eight per thread in flight, and each column then reads only LDS.  Ranges beyond the
+// LDS capacity read their rows from memory.  Bound by the loads in flight: with 256 columns and
+// 53 KB of LDS a workgroup three fitted a CU, now five of twice the threads per column do.  Two
+// rows per column: 2,048 problems of N = 2,048, w = 12 265 -> 207 us; 200 of N = 1,000, w = 20
+// 75 -> 18 (the range of 256 columns did not fit LDS); one row per column, 500 of N = 1,000,
+// w = 4 14.3 -> 15.9.
+constexpr int kJtCols = 128;  // columns of a workgroup
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_banded_jt(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__ row_start, const int32_t* __restrict__ fr,
             const T* __restrict__ vals, const double* __restrict__ r, const double* __restrict__ d,
             const double* __restrict__ lamv, const double* __restrict__ v, double* __restrict__ g) {
-  constexpr int CAP = 1024;                          // rows
-  constexpr int VCAP = 40960 / (int)sizeof(T);       // values
+  constexpr int CAP = 576;                           // rows
+  constexpr int VCAP = 24576 / (int)sizeof(T);       // values
   __shared__ int32_t s_st[CAP];
   __shared__ double s_r[CAP];
   __shared__ T s_v[VCAP];
-  const int64_t nb = (N + 255) / 256;
+  const int64_t nb = (N + kJtCols - 1) / kJtCols;
   const int64_t prob = blockIdx.x / nb;
-  const int64_t c0 = (int64_t)(blockIdx.x % nb) * 256;
-  const int64_t j = c0 + threadIdx.x;
+  const int64_t c0 = (int64_t)(blockIdx.x % nb) * kJtCols;
+  const int64_t j = c0 + (threadIdx.x >> 1);
+  const int half = threadIdx.x & 1;
   const int32_t* rs = row_start + prob * M;
   const int32_t* f = fr + prob * (N + 1);
   const double* rp = r + prob * M;
@@ -159,7 +166,7 @@ k_banded_jt(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__ row_
     return i < 0 ? 0 : (i > M ? M : i);
   };
   const int64_t lo = row_at(c0 - w + 1);
-  int64_t hi = row_at(c0 + 256);
+  int64_t hi = row_at(c0 + kJtCols);
   hi = hi < lo ? lo : hi;
   const int64_t n = hi - lo;
   const bool staged = n <= CAP && n * w <= VCAP;
@@ -205,35 +212,37 @@ k_banded_jt(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__ row_
   if (staged) {
     a = a < lo ? lo : a;
     e = e > hi ? hi : e;
-    // eight rows per batch: their LDS reads are independent, the sum keeps row order
+    // four rows per batch: their LDS reads are independent, the sum keeps row order
     const int i1 = (int)(e - lo);
-    for (int i0 = (int)(a - lo); i0 < i1; i0 += 8) {
-      int kk[8];
-      double rr[8];
+    for (int i0 = (int)(a - lo) + half; i0 < i1; i0 += 8) {
+      int kk[4];
+      double rr[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = i0 + u < i1 ? i0 + u : i1 - 1;
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + 2 * u < i1 ? i0 + 2 * u : i0;
         kk[u] = (int)(j - s_st[i]);
         rr[u] = s_r[i];
       }
-      T vv[8];
+      T vv[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = i0 + u < i1 ? i0 + u : i1 - 1;
+      for (int u = 0; u < 4; ++u) {
+        const int i = i0 + 2 * u < i1 ? i0 + 2 * u : i0;
         const int k = kk[u] < 0 ? 0 : (kk[u] >= w ? w - 1 : kk[u]);
         vv[u] = s_v[i * w + k];
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (i0 + u < i1 && kk[u] >= 0 && kk[u] < w) acc += (double)vv[u] * rr[u];
+      for (int u = 0; u < 4; ++u)
+        if (i0 + 2 * u < i1 && kk[u] >= 0 && kk[u] < w) acc += (double)vv[u] * rr[u];
     }
   } else {
-    for (int64_t i = a; i < e; ++i) {
+    for (int64_t i = a + half; i < e; i += 2) {
       const int64_t k = j - band_start(rs, i, N, w);
       if (k < 0 || k >= w) continue;
       acc += (double)V[i * w + k] * rp[i];
     }
   }
+  acc += __shfl_xor(acc, 1, kWave);
+  if (half) return;
   const int64_t t = prob * N + j;
   const double dj = d[t];
   g[t] = acc - lamv[prob] * dj * dj * v[t];
@@ -331,7 +340,7 @@ template <typename T>
 hipError_t launch_banded_jt(int P, int64_t M, int64_t N, int w, const int32_t* row_start, const int32_t* fr,
                             const T* vals, const double* r, const double* d, const double* lam, const double* v,
                             double* g, hipStream_t st) {
-  const int64_t blocks = (int64_t)P * ((N + 255) / 256);
+  const int64_t blocks = (int64_t)P * ((N + kJtCols - 1) / kJtCols);
   hipLaunchKernelGGL((k_banded_jt<T>), dim3((unsigned)blocks), dim3(256), 0, st, P, M, N, w, row_start, fr, vals, r,
                      d, lam, v, g);
   return hipGetLastError();
