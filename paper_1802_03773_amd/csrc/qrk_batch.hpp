@@ -43,18 +43,16 @@ struct ProbDesc {
   int64_t soff;           // S_p|c_p (K x n x L, row stride L) at element soff
   int64_t redoff, ldr;    // reduced rows (M x ldr) at element redoff
   int64_t rboff;          // R_B|c_B (L x L, row-major) at element rboff
-  int64_t slot0, ctr0;    // merge tree: first slot float, first arrival counter
+  int64_t slot0, ctr0;    // merge tree: first slot element, first flag
   int64_t rows_per_leaf;  // dense-part QR: rows per leaf
   int64_t pack0, npacks;  // packs of whole blocks (global index of the first)
   int32_t nB, L;          // coupled columns, L = nB + 1
   int32_t leaves;         // dense-part QR leaves
   int32_t wg0, nwg;       // refinement workgroups [wg0, wg0 + nwg)
-  int32_t tree_sep;       // 1: the leaves only store their triangles; a separate launch merges them
-  int32_t pad;
 };
 
 // Work the first per-block QR launch of a factor call does before its blocks: workgroup 0
-// clears z0[0..n0) and z1[0..n1) (status words, merge-tree arrival counters), and when
+// clears z0[0..n0) and z1[0..n1) (status words, merge-tree flags), and when
 // lam_out is set every block uses lam_val for lambda and thread 0 of workgroup 0 stores it
 // to *lam_out for the later kernels (which run after the launch completes).
 struct BqrPrologue {
@@ -64,6 +62,16 @@ struct BqrPrologue {
   int64_t n1 = 0;
   double* lam_out = nullptr;
   double lam_val = 0.0;
+};
+
+// Merge nodes of the problems of one column-block count (pipelined tree): entries [begin, begin +
+// count) of the node tables -- problem, index within its tree, children.
+struct TreeNodes {
+  int begin = 0, count = 0;
+  const int32_t* prob = nullptr;
+  const int32_t* idx = nullptr;
+  const int32_t* l = nullptr;
+  const int32_t* r = nullptr;
 };
 
 // Stored Q of a problem's dense part (in an array of its own, so that the kernels without the

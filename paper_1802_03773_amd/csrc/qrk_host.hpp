@@ -68,14 +68,14 @@ struct qrk_handle_s {
   int64_t slot_cap = 0;          // elements
   int64_t ctr_cap = 0;           // ints
   int64_t nctr = 1;              // counters in use
-  // pipelined merge trees (tree_sep): the inner nodes' problems, indices and child references,
+  // merge trees: the inner nodes' problems, indices and child references,
   // grouped by column-block count, in level order over a count's problems
   int32_t* node_prob = nullptr;
   int32_t* node_idx = nullptr;
   int32_t* node_l = nullptr;
   int32_t* node_r = nullptr;
   int node_begin[9] = {0};
-  int node_count[9] = {0};       // all 0: the merges run inside the leaf launch
+  int node_count[9] = {0};
   int cls_begin[9] = {0};        // float32 leaves grouped by 16-column-block count, widest first
   int queue_begin = 0;           // first leaf of the persistent launch (classes 6 .. 1)
   int64_t qhead_off = 0;         // its queue head among the counters

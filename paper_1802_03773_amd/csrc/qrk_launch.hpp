@@ -54,13 +54,10 @@ int tsqr_mfma_slot_floats(int L);
 // p[0 .. n) = 0 (a kernel, so it may be captured into a graph).
 hipError_t launch_zero_ints(int* p, int64_t n, hipStream_t st);
 
-// Pipelined merge tree of a single problem whose leaves stored their triangles (tree_sep):
-// nnodes inner nodes in level order (node_l / node_r child references, r < 0 leaf -1 - r),
-// flags[nnodes * ncb] cleared beforehand; ncb <= kTreeMaxNCB.  The root writes R_B | c_B.
-constexpr int kTreeMaxNCB = 8;
-hipError_t launch_tsqr_tree(int ncb, const ProbDesc* probs, const int32_t* node_l, const int32_t* node_r,
-                            int nnodes, float* slots, int* flags, float* RB, int* status, const QStore& qs,
-                            hipStream_t st);
+// Pipelined merge trees of the problems with ncb column blocks whose leaves stored their triangles:
+// one wave per inner node; flags are cleared by the factor call's first launch.
+hipError_t launch_tsqr_tree(int ncb, const ProbDesc* probs, const TreeNodes& tn, float* slots, int* flags, float* RB,
+                            int* status, const QStore& qs, hipStream_t st);
 // Leaves of classes 8 and 7 by their launches; the leaves from queue_begin on (classes
 // kQueueNCB .. 1, listed widest first) by one persistent launch of at most `cus` workgroups
 // that takes them from the device counter *qhead (cleared with the counters) when use_queue is
@@ -68,8 +65,7 @@ hipError_t launch_tsqr_tree(int ncb, const ProbDesc* probs, const int32_t* node_
 hipError_t launch_tsqr_mfma(bool bf16x3, const int* cls_begin, const int* cls_count, int queue_begin, bool use_queue,
                             int cus,
                             const int32_t* leaf_prob, const int32_t* leaf_idx, const ProbDesc* probs, int n,
-                            const float* Red, const double* d, const double* lam, float* slots, int* counters,
-                            int64_t nctr, int* qhead, float* RB, const QStore& qs, hipStream_t st);
+                            const float* Red, const double* d, const double* lam, float* slots, int64_t nctr, int* qhead, float* RB, const QStore& qs, hipStream_t st);
 
 // R_B p_B = c_B for every problem (RB_p is L x L with c_B in column L-1, or c_B from cext,
 // laid out like p, when that is given); writes p_B.

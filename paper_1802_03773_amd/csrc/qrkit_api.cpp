@@ -78,7 +78,7 @@ qrk_status factor_ba(qrk_handle h, hipStream_t st, const double* lam_host = null
   T* Sc = static_cast<T*>(h->Sc);
   T* Red = static_cast<T*>(h->Red);
   T* RB = static_cast<T*>(h->RB);
-  // the first launch clears the status words and the merge-tree arrival counters
+  // the first launch clears the status words and the merge-tree flags
   BqrPrologue pro;
   pro.z0 = h->status;
   pro.n0 = h->P;
@@ -117,14 +117,20 @@ qrk_status factor_ba(qrk_handle h, hipStream_t st, const double* lam_host = null
     float* slots = static_cast<float*>(h->slots);
     pr = prof_begin(h, 1, st);
     if (launch_tsqr_mfma(h->mode == QRK_BF16X3, h->cls_begin, h->cls_count, h->queue_begin, h->leaf_queue != 0, h->cus,
-                         h->leaf_prob, h->leaf_idx, h->probs_d, h->n, Red, h->d, h->lam_ptr, slots, h->counters,
+                         h->leaf_prob, h->leaf_idx, h->probs_d, h->n, Red, h->d, h->lam_ptr, slots,
                          h->nctr, h->counters + h->qhead_off, RB, qs, st) != hipSuccess)
       return QRK_EHIP;
-    const int ncb0 = (h->probs_h[0].L + 15) / 16;
-    if (h->node_count[ncb0] > 0 &&
-        launch_tsqr_tree(ncb0, h->probs_d, h->node_l, h->node_r, h->node_count[ncb0], slots, h->counters, RB,
-                         h->status, qs, st) != hipSuccess)
-      return QRK_EHIP;
+    for (int c = 8; c >= 1; --c) {
+      TreeNodes tn;
+      tn.begin = h->node_begin[c];
+      tn.count = h->node_count[c];
+      tn.prob = h->node_prob;
+      tn.idx = h->node_idx;
+      tn.l = h->node_l;
+      tn.r = h->node_r;
+      if (launch_tsqr_tree(c, h->probs_d, tn, slots, h->counters, RB, h->status, qs, st) != hipSuccess)
+        return QRK_EHIP;
+    }
     prof_end(h, pr, st);
     h->q_valid = keep;
     return QRK_OK;
@@ -239,31 +245,26 @@ void dfree(qrk_handle h, void* ptr) {
     }
 }
 
-// Slots and arrival counters a merge tree over `leaves` leaves touches: level k has n_k
-// nodes (n_0 = leaves, n_{k+1} = ceil(n_k / 2)); its stored triangles sit at slots
-// [sum_{j<k} n_j, sum_{j<=k} n_j) and its counters at [sum_{j<k} n_{j+1}, ...).
-struct TreeSize {
-  int64_t slots, counters;
-};
-TreeSize tree_size(int64_t leaves) {
-  TreeSize t{0, 0};
-  for (int64_t nl = leaves; nl > 1; nl = (nl + 1) / 2) {
-    t.slots += nl;
-    t.counters += (nl + 1) / 2;
-  }
-  t.slots = std::max<int64_t>(t.slots, 1);
-  t.counters = std::max<int64_t>(t.counters, 1);
-  return t;
+// Slots of a merge tree over `leaves` leaves by levels (the stored Q's application): level k has
+// n_k nodes (n_0 = leaves, n_{k+1} = ceil(n_k / 2)).
+int64_t tree_level_slots(int64_t leaves) {
+  int64_t slots = 0;
+  for (int64_t nl = leaves; nl > 1; nl = (nl + 1) / 2) slots += nl;
+  return std::max<int64_t>(slots, 1);
 }
 
 // Dense-part leaves of every problem (single waves).  float32: per 16-column-block class c the
 // default is about max(a tile, rows_c / 4096) rows per leaf (rows_c: the class's reduced plus
-// damping rows; in batches, whose merges use BF16x3 products in that mode, 128 instead of a tile),
+// damping rows; 128 rows in batches),
 // scaled by leaf_scale; float64: a tile of the class, or more in whole tiles so that a
 // class's leaves are about one round of waves.  At most 1024 leaves per problem; a single-problem
-// handle may fix the count (h->leaves > 0).  Leaves are listed class by class for the per-class
-// launches, and each problem's merge tree gets the slots and the arrival counters (or flags) it
-// needs.
+// handle may fix the count (h->leaves > 0).  Leaves and merge nodes are listed class by class for
+// the per-class launches, and each problem's merge tree gets the slots and the flags it needs.
+// Every tree is a launch of its own, pipelined over column blocks.  Merging a float32 batch's
+// leaves inside their launch, the second wave of a pair to finish doing a whole merge, was slower
+// at every size: 4 problems of 300 blocks with 30 columns 104 against 85 us a step, 16 of 450 with
+// 90 435 against 211, 128 of 1,250 with 6, 30 or 90 2,718 against 1,691, 128 of 2,250 with 63
+// 2,736 against 2,157.
 qrk_status assign_leaves(qrk_handle h) {
   std::vector<ProbDesc>& pd = h->probs_h;
   const int P = h->P;
@@ -300,9 +301,7 @@ qrk_status assign_leaves(qrk_handle h) {
           }
       h->cls_count[c] = (int)lp.size() - h->cls_begin[c];
     }
-    // float64 problems and a float32 problem by itself merge their leaves in a separate launch,
-    // pipelined over column blocks; in a float32 batch the merges run inside the leaf launch
-    const bool sep = f64 || P == 1;
+    // the merge trees are launches of their own, pipelined over column blocks
     std::vector<int32_t> np, ni, nl, nr;
     for (int c = 8; c >= 1; --c) {
       h->node_begin[c] = (int)np.size();
@@ -311,7 +310,7 @@ qrk_status assign_leaves(qrk_handle h) {
       std::vector<int32_t> made((size_t)P, 0);
       bool any = false;
       for (int q = 0; q < P; ++q)
-        if (sep && (pd[q].L + 15) / 16 == c && pd[q].leaves > 1) {
+        if ((pd[q].L + 15) / 16 == c && pd[q].leaves > 1) {
           items[(size_t)q].resize((size_t)pd[q].leaves);
           for (int i = 0; i < pd[q].leaves; ++i) items[(size_t)q][(size_t)i] = -1 - i;
           any = true;
@@ -341,15 +340,8 @@ qrk_status assign_leaves(qrk_handle h) {
       const int64_t tri = f64 ? tsqr64_slot_doubles(D.L) : tsqr_mfma_slot_floats(D.L);
       D.slot0 = slot;
       D.ctr0 = ctr;
-      D.tree_sep = sep && D.leaves > 1 ? 1 : 0;
-      if (D.tree_sep) {
-        slot += (2 * (int64_t)D.leaves - 1) * tri;
-        ctr += (int64_t)(D.leaves - 1) * ((D.L + 15) / 16) * 2;  // two flags per column block
-      } else {
-        const TreeSize ts = tree_size(D.leaves);
-        slot += ts.slots * tri;
-        ctr += ts.counters;
-      }
+      slot += (2 * (int64_t)D.leaves - 1) * tri;
+      ctr += (int64_t)(D.leaves - 1) * ((D.L + 15) / 16) * 2;  // two flags per column block
     }
     // stored Q: tile panels of every leaf, node panels of the leaves - 1 merges, and the
     // application's merge vectors (128 floats per tree slot)
@@ -365,7 +357,7 @@ qrk_status assign_leaves(qrk_handle h) {
       O.qn0 = qn;
       qn += (int64_t)(D.leaves - 1) * node_panel_off(ncb);
       O.qc0 = qu;
-      qu += tree_size(D.leaves).slots * 128;
+      qu += tree_level_slots(D.leaves) * 128;
     }
     h->q_tiles_n = std::max<int64_t>(qt, 1);
     h->q_nodes_n = std::max<int64_t>(qn, 1);

@@ -9,11 +9,8 @@
 //   * every wave is a leaf of one problem: it streams a contiguous range of that problem's
 //     rows, a tile of 16*NRB rows at a time, into its own running upper triangle R (a flat
 //     tree inside the wave);
-//   * the leaf triangles of each problem are then merged pairwise, QR([R_left; R_right]),
-//     in the same launch: the second wave of a pair to finish performs the merge (arrival
-//     counted with a device-scope atomic), so no wave ever waits for another, and the trees
-//     of different problems proceed independently;
-//   * each problem's root is written out row-major (L x L).
+//   * the leaf triangles of each problem are stored, and merged pairwise by a launch of their
+//     own (tsqr_tree.hpp); a problem of one leaf writes its triangle out row-major (L x L).
 //
 // Merging a tile X into R uses blocked Householder with the compact WY form (paper
 // Section 2, compressed WY: Q = I - V T V^T; the paper writes I + Y T Y^T, the sign of
@@ -276,21 +273,17 @@ __device__ __forceinline__ void tri_put(f4 (&R)[Tri<NCB>::count], float* rl, int
 }
 
 // Merge the tile X (NRB block rows) into the running triangle R.
-//   TRI = false: a dense tile of 16*NRB rows; panels before pstart are skipped (their
-//                tile columns are known to be zero).
-//   TRI = true : the tile is an upper-triangular NCB x NCB block triangle (NRB == NCB);
-//                in panel P only block rows 0..P are nonzero, which is used at compile
-//                time.
+// X is a dense tile of 16*NRB rows; panels before pstart are skipped (their tile columns are
+// known to be zero).
 // The Householder vectors are kept unscaled: the tile column x_j stays in place and the
 // reflector's tile part is w_j = s_j x_j with s_j = 1/(alpha_j - beta_j); the scales are
 // applied once per row of the small Z products instead of once per tile element.
 // Only the first NPANEL panels are factored; their reflectors are still applied to every
 // column block (the later blocks then hold columns that are carried, not factored).
 // KEEPQ: the panels' compact-WY factors (T, the scales and the raw reflector blocks,
-// qrk_batch.hpp) are stored at qkeep for a later Q^T: panel P at P * tile_panel_floats for a
-// dense tile, at TreeKeep<NCB>::off(P) for a triangle.
+// qrk_batch.hpp) are stored at qkeep for a later Q^T, panel P at P * tile_panel_floats.
 // RL < NCB: R's block rows from RL on are in LDS at rl (TriSplit).
-template <int NCB, int NRB, bool TRI, bool BF = false, int NPANEL = NCB, bool FUSE = false, bool KEEPQ = false,
+template <int NCB, int NRB, bool BF = false, int NPANEL = NCB, bool FUSE = false, bool KEEPQ = false,
           int RL = NCB>
 __device__ __forceinline__ void merge_tile(f4 (&R)[Tri<NCB>::count], f4 (&X)[NRB][NCB], int pstart,
                                            float* __restrict__ lds, int lane, float* __restrict__ qkeep = nullptr,
@@ -304,8 +297,8 @@ __device__ __forceinline__ void merge_tile(f4 (&R)[Tri<NCB>::count], f4 (&X)[NRB
   static_for<0, NCB>([&](auto PP) {
     constexpr int P = decltype(PP)::value;
     constexpr int rp = Tri<NCB>::idx(P, P);
-    constexpr int RBN = TRI ? (P + 1 < NRB ? P + 1 : NRB) : NRB;  // active block rows
-    if (!TRI && P < pstart) return;
+    constexpr int RBN = NRB;  // active block rows
+    if (P < pstart) return;
     if constexpr (P >= NPANEL) return;
 
     // ---- panel factorisation of [R[P][P]; X[:, P]] (and T alongside) -------------------
@@ -342,7 +335,7 @@ __device__ __forceinline__ void merge_tile(f4 (&R)[Tri<NCB>::count], f4 (&X)[NRB
       // T, the scales and W of this panel, from the registers they are staged from: lane (0, c)
       // holds row c of T (trow) and scale c, lane (g, c) the entries 4g .. 4g+3 of W's column c
       // in each block
-      float* qp = qkeep + (TRI ? (int64_t)TreeKeep<NCB>::off(P) : P * tile_panel_floats(NRB));
+      float* qp = qkeep + P * tile_panel_floats(NRB);
       if (g == 0) {
 #pragma unroll
         for (int k = 0; k < 16; k += 4)
@@ -467,7 +460,7 @@ __device__ __forceinline__ void merge_tile(f4 (&R)[Tri<NCB>::count], f4 (&X)[NRB
 }
 
 // A stored triangle is its NCB(NCB+1)/2 blocks, 1 KiB each, lane-contiguous.
-// RL < NCB: the blocks from TriSplit<NCB, RL>::first on are read from / written to the LDS rows.
+// RL < NCB: the blocks from TriSplit<NCB, RL>::first on are read from the LDS rows.
 template <int NCB, int RL = NCB>
 __device__ __forceinline__ void store_tri(float* __restrict__ dst, const f4 (&R)[Tri<NCB>::count],
                                           int lane, const float* __restrict__ rl = nullptr) {
@@ -478,56 +471,20 @@ __device__ __forceinline__ void store_tri(float* __restrict__ dst, const f4 (&R)
         t < first ? R[t] : *reinterpret_cast<const f4*>(rl + (t - first) * 256 + lane * 4);
 }
 
-template <int NCB, int RL = NCB>
-__device__ __forceinline__ void load_tri(const float* __restrict__ src, f4 (&R)[Tri<NCB>::count],
-                                         int lane, float* __restrict__ rl = nullptr) {
-  constexpr int first = TriSplit<NCB, RL>::first;
-#pragma unroll
-  for (int t = 0; t < Tri<NCB>::count; ++t) {
-    const f4 v = __builtin_nontemporal_load(reinterpret_cast<const f4*>(src + t * 256 + lane * 4));
-    if (t < first)
-      R[t] = v;
-    else
-      *reinterpret_cast<f4*>(rl + (t - first) * 256 + lane * 4) = v;
-  }
-}
-
-// R <- triangle of QR([R; stored triangle at src]).
-template <int NCB, bool BF = false, bool KEEPQ = false, int RL = NCB>
-__device__ __forceinline__ void merge_stored_tri(f4 (&R)[Tri<NCB>::count], const float* __restrict__ src,
-                                                 float* lds, int lane, float* __restrict__ qkeep = nullptr,
-                                                 float* __restrict__ rl = nullptr) {
-  f4 X[NCB][NCB];
-  static_for<0, NCB>([&](auto RB) {
-    constexpr int rb = decltype(RB)::value;
-    static_for<0, NCB>([&](auto QQ) {
-      constexpr int q = decltype(QQ)::value;
-      if constexpr (q >= rb)
-        X[rb][q] = __builtin_nontemporal_load(
-            reinterpret_cast<const f4*>(src + Tri<NCB>::idx(rb, q) * 256 + lane * 4));
-      else
-        X[rb][q] = f4{0.f, 0.f, 0.f, 0.f};
-    });
-  });
-  merge_tile<NCB, NCB, true, BF, NCB, false, KEEPQ, RL>(R, X, 0, lds, lane, qkeep, rl);
-}
-
 // One leaf of the dense part, by one wave: leaf li of problem p streams rows
 // [li * rows_per_leaf, ...) of the problem's reduced rows into its triangle (leaf 0 starts from
-// diag(sqrt(lam_p) d_B)); the leaves of each problem are then merged pairwise (the problem's own
-// slots and arrival counters: the second wave of a pair to finish merges) and the root is
-// written row-major to the problem's R_B | c_B.
+// diag(sqrt(lam_p) d_B)) and stores it at its slot for the merge tree's launch; a problem of one
+// leaf writes it row-major to its R_B | c_B.
 // KEEP (the stored Q): the panels of the leaf's tiles go to qs.qt (at the problem's qt0, qtiles
-// tiles per leaf) and those of its merges to qs.qn (at qn0, one TreeKeep per merge node, numbered
-// level by level from the leaves up as the separate merge tree numbers its nodes).  A separate
-// instantiation, so that the kernels without it are compiled as if it did not exist.
+// tiles per leaf).  A separate instantiation, so that the kernels without it are compiled as if
+// it did not exist.
 // RL < NCB: the running triangle's block rows from RL on are kept in the wave's LDS at rl
 // (TriSplit) instead of registers.
 template <int NCB, int NRB, bool BF, bool KEEP = false, int RL = NCB>
 __device__ __forceinline__ void tsqr_leaf(int pi, int leaf, const ProbDesc* __restrict__ probs, int n,
                                           const float* __restrict__ Red, const double* __restrict__ d,
                                           const double* __restrict__ lamv, float* __restrict__ slots,
-                                          int* __restrict__ counters, float* __restrict__ RBall, float* lds,
+                                          float* __restrict__ RBall, float* lds,
                                           int lane, const QStore qs = QStore(), float* __restrict__ rl = nullptr) {
   static_assert(!KEEP || RL == NCB, "the stored Q's leaves keep the triangle in registers");
   const ProbDesc& P = probs[pi];
@@ -584,58 +541,18 @@ __device__ __forceinline__ void tsqr_leaf(int pi, int leaf, const ProbDesc* __re
     if constexpr (KEEP) {
       const int64_t tile = (t - r0) / KT;
       float* qk = qs.qt + qs.qo[pi].qt0 + ((int64_t)leaf * qs.qo[pi].qtiles + tile) * (NCB * tile_panel_floats(NRB));
-      merge_tile<NCB, NRB, false, BF, NCB, false, true>(R, X, 0, lds, lane, qk);
+      merge_tile<NCB, NRB, BF, NCB, false, true>(R, X, 0, lds, lane, qk);
     } else {
-      merge_tile<NCB, NRB, false, BF, NCB, false, false, RL>(R, X, 0, lds, lane, nullptr, rl);
+      merge_tile<NCB, NRB, BF, NCB, false, false, RL>(R, X, 0, lds, lane, nullptr, rl);
     }
   }
 
-  // ---- pairwise merges up the problem's tree, in the same launch ----------------------------
-  float* pslots = slots + P.slot0;
-  if (P.tree_sep && nleaves > 1) {  // the merges are a separate, pipelined launch
-    store_tri<NCB, RL>(pslots + (int64_t)leaf * SLOT, R, lane, rl);
+  if (nleaves > 1) {  // the merge tree is a launch of its own (tsqr_tree.hpp)
+    store_tri<NCB, RL>(slots + P.slot0 + (int64_t)leaf * SLOT, R, lane, rl);
     return;
   }
-  int* pctr = counters + P.ctr0;
-  int nl = nleaves;
-  int slot = leaf;
-  int64_t base = 0;   // first slot of the current level
-  int64_t cbase = 0;  // first counter of the current level
-  int64_t mbase = 0;  // merges of the levels below (the stored Q's node numbering)
-  while (nl > 1) {
-    const int sib = slot ^ 1;
-    const int parent = slot >> 1;
-    const int nn = (nl + 1) >> 1;
-    if (sib >= nl) {  // no sibling at this level: carry the triangle up unchanged
-      base += nl;
-      cbase += nn;
-      if constexpr (KEEP) mbase += nl >> 1;
-      slot = parent;
-      nl = nn;
-      continue;
-    }
-    store_tri<NCB, RL>(pslots + (base + slot) * SLOT, R, lane, rl);
-    __threadfence();
-    int old = 0;
-    if (lane == 0) old = atomicAdd(&pctr[cbase + parent], 1);
-    old = __builtin_amdgcn_readfirstlane(old);
-    if (old == 0) return;  // the sibling is still running; it will merge
-    __threadfence();
-    const int left = slot & ~1;
-    load_tri<NCB, RL>(pslots + (base + left) * SLOT, R, lane, rl);
-    if constexpr (KEEP)
-      merge_stored_tri<NCB, BF, true>(R, pslots + (base + left + 1) * SLOT, lds, lane,
-                                      qs.qn + qs.qo[pi].qn0 + (mbase + parent) * TreeKeep<NCB>::total);
-    else
-      merge_stored_tri<NCB, BF, false, RL>(R, pslots + (base + left + 1) * SLOT, lds, lane, nullptr, rl);
-    base += nl;
-    cbase += nn;
-    if constexpr (KEEP) mbase += nl >> 1;
-    slot = parent;
-    nl = nn;
-  }
 
-  // ---- root: row-major L x L ----------------------------------------------------------------
+  // ---- a single leaf: the root, row-major L x L ---------------------------------------------
   float* Rout = RBall + P.rboff;
   static_for<0, NCB>([&](auto PP) {
     constexpr int Q = decltype(PP)::value;
@@ -673,7 +590,7 @@ __global__ void __launch_bounds__(256)
 k_tsqr_mfma(int leaf_begin, int nleaves_cls, const int32_t* __restrict__ leaf_prob,
             const int32_t* __restrict__ leaf_idx, const ProbDesc* __restrict__ probs, int n,
             const float* __restrict__ Red, const double* __restrict__ d, const double* __restrict__ lamv,
-            float* __restrict__ slots, int* __restrict__ counters, float* __restrict__ RBall) {
+            float* __restrict__ slots, float* __restrict__ RBall) {
   __shared__ float lds_all[4][kWaveLds];
   const int lane = threadIdx.x & 63;
   const int wv = threadIdx.x >> 6;
@@ -683,10 +600,10 @@ k_tsqr_mfma(int leaf_begin, int nleaves_cls, const int32_t* __restrict__ leaf_pr
     constexpr int RL = leaf_lds_rows(NCB);
     __shared__ float rl_all[4][TriSplit<NCB, RL>::lds_blocks * 256];
     tsqr_leaf<NCB, NRB, BF, false, RL>(leaf_prob[leaf_begin + wl], leaf_idx[leaf_begin + wl], probs, n, Red, d,
-                                       lamv, slots, counters, RBall, lds_all[wv], lane, QStore(), rl_all[wv]);
+                                       lamv, slots, RBall, lds_all[wv], lane, QStore(), rl_all[wv]);
   } else {
     tsqr_leaf<NCB, NRB, BF>(leaf_prob[leaf_begin + wl], leaf_idx[leaf_begin + wl], probs, n, Red, d, lamv, slots,
-                            counters, RBall, lds_all[wv], lane);
+                            RBall, lds_all[wv], lane);
   }
 }
 template <int NCB, int NRB, bool BF>
@@ -694,14 +611,14 @@ __global__ void __launch_bounds__(256)
 k_tsqr_mfma_keep(int leaf_begin, int nleaves_cls, const int32_t* __restrict__ leaf_prob,
                  const int32_t* __restrict__ leaf_idx, const ProbDesc* __restrict__ probs, int n,
                  const float* __restrict__ Red, const double* __restrict__ d, const double* __restrict__ lamv,
-                 float* __restrict__ slots, int* __restrict__ counters, float* __restrict__ RBall, const QStore qs) {
+                 float* __restrict__ slots, float* __restrict__ RBall, const QStore qs) {
   __shared__ float lds_all[4][kWaveLds];
   const int lane = threadIdx.x & 63;
   const int wv = threadIdx.x >> 6;
   const int wl = blockIdx.x * 4 + wv;
   if (wl >= nleaves_cls) return;
   tsqr_leaf<NCB, NRB, BF, true>(leaf_prob[leaf_begin + wl], leaf_idx[leaf_begin + wl], probs, n, Red, d, lamv, slots,
-                                counters, RBall, lds_all[wv], lane, qs);
+                                RBall, lds_all[wv], lane, qs);
 }
 
 // Leaf tile blocks of 16 rows for each column-block count (leaf_tile_rows, qrk_batch.hpp).
@@ -714,8 +631,7 @@ struct LeafTile {
 // The leaves of every problem with at most kQueueNCB column blocks in one persistent launch:
 // each wave takes the next item of the leaf list (widest problems first) from a device-scope
 // counter until the list is exhausted, and runs that leaf with the body instantiated for its
-// problem's column-block count.  A wave that finds its merge partner still running goes on to
-// the next item.  Every leaf body needs the whole register file (one wave per SIMD), so one
+// problem's column-block count.  Every leaf body needs the whole register file (one wave per SIMD), so one
 // launch over all widths costs no occupancy against one launch per width, and the narrow
 // problems' leaves fill the SIMDs that the wide ones leave idle at the end.  kQueueNCB (the
 // widest count in the queue) is in qrk_batch.hpp.
@@ -727,18 +643,18 @@ template <int NCB, bool BF>
 __device__ __noinline__ void tsqr_leaf_call(int pi, int leaf, const ProbDesc* __restrict__ probs, int n,
                                             const float* __restrict__ Red, const double* __restrict__ d,
                                             const double* __restrict__ lamv, float* __restrict__ slots,
-                                            int* __restrict__ counters, float* __restrict__ RBall, float* lds,
+                                            float* __restrict__ RBall, float* lds,
                                             int lane, float* rl) {
   tsqr_leaf<NCB, LeafTile<NCB>::nrb, BF, false, leaf_lds_rows(NCB)>(pi, leaf, probs, n, Red, d, lamv, slots,
-                                                                     counters, RBall, lds, lane, QStore(), rl);
+                                                                     RBall, lds, lane, QStore(), rl);
 }
 template <int NCB, bool BF>
 __device__ __noinline__ void tsqr_leaf_call_keep(int pi, int leaf, const ProbDesc* __restrict__ probs, int n,
                                                  const float* __restrict__ Red, const double* __restrict__ d,
                                                  const double* __restrict__ lamv, float* __restrict__ slots,
-                                                 int* __restrict__ counters, float* __restrict__ RBall, float* lds,
+                                                 float* __restrict__ RBall, float* lds,
                                                  int lane, const QStore qs) {
-  tsqr_leaf<NCB, LeafTile<NCB>::nrb_keep, BF, true>(pi, leaf, probs, n, Red, d, lamv, slots, counters, RBall, lds, lane,
+  tsqr_leaf<NCB, LeafTile<NCB>::nrb_keep, BF, true>(pi, leaf, probs, n, Red, d, lamv, slots, RBall, lds, lane,
                                                qs);
 }
 
@@ -749,7 +665,7 @@ __device__ __forceinline__ void tsqr_queue_loop(int nitems, const int32_t* __res
                                                 const ProbDesc* __restrict__ probs, int n,
                                                 const float* __restrict__ Red, const double* __restrict__ d,
                                                 const double* __restrict__ lamv, float* __restrict__ slots,
-                                                int* __restrict__ counters, int* __restrict__ qhead,
+                                                int* __restrict__ qhead,
                                                 float* __restrict__ RBall, const QStore& qs) {
   __shared__ float lds_all[4][kWaveLds];
   const int lane = threadIdx.x & 63;
@@ -770,9 +686,9 @@ __device__ __forceinline__ void tsqr_queue_loop(int nitems, const int32_t* __res
 #define QRK_QLEAF(C)                                                                                          \
   case C:                                                                                                     \
     if constexpr (KEEP)                                                                                       \
-      tsqr_leaf_call_keep<C, BF>(pi, leaf, probs, n, Red, d, lamv, slots, counters, RBall, lds, lane, qs);    \
+      tsqr_leaf_call_keep<C, BF>(pi, leaf, probs, n, Red, d, lamv, slots, RBall, lds, lane, qs);    \
     else                                                                                                      \
-      tsqr_leaf_call<C, BF>(pi, leaf, probs, n, Red, d, lamv, slots, counters, RBall, lds, lane, rl);         \
+      tsqr_leaf_call<C, BF>(pi, leaf, probs, n, Red, d, lamv, slots, RBall, lds, lane, rl);         \
     break;
       QRK_QLEAF(1) QRK_QLEAF(2) QRK_QLEAF(3) QRK_QLEAF(4) QRK_QLEAF(5) QRK_QLEAF(6)
 #undef QRK_QLEAF
@@ -786,9 +702,8 @@ template <bool BF>
 __global__ void __launch_bounds__(256)
 k_tsqr_queue(int nitems, const int32_t* __restrict__ leaf_prob, const int32_t* __restrict__ leaf_idx,
              const ProbDesc* __restrict__ probs, int n, const float* __restrict__ Red, const double* __restrict__ d,
-             const double* __restrict__ lamv, float* __restrict__ slots, int* __restrict__ counters,
-             int* __restrict__ qhead, float* __restrict__ RBall) {
-  tsqr_queue_loop<BF, false>(nitems, leaf_prob, leaf_idx, probs, n, Red, d, lamv, slots, counters, qhead, RBall,
+             const double* __restrict__ lamv, float* __restrict__ slots, int* __restrict__ qhead, float* __restrict__ RBall) {
+  tsqr_queue_loop<BF, false>(nitems, leaf_prob, leaf_idx, probs, n, Red, d, lamv, slots, qhead, RBall,
                              QStore());
 }
 template <bool BF>
@@ -796,14 +711,14 @@ __global__ void __launch_bounds__(256)
 k_tsqr_queue_keep(int nitems, const int32_t* __restrict__ leaf_prob, const int32_t* __restrict__ leaf_idx,
                   const ProbDesc* __restrict__ probs, int n, const float* __restrict__ Red,
                   const double* __restrict__ d, const double* __restrict__ lamv, float* __restrict__ slots,
-                  int* __restrict__ counters, int* __restrict__ qhead, float* __restrict__ RBall, const QStore qs) {
-  tsqr_queue_loop<BF, true>(nitems, leaf_prob, leaf_idx, probs, n, Red, d, lamv, slots, counters, qhead, RBall, qs);
+                  int* __restrict__ qhead, float* __restrict__ RBall, const QStore qs) {
+  tsqr_queue_loop<BF, true>(nitems, leaf_prob, leaf_idx, probs, n, Red, d, lamv, slots, qhead, RBall, qs);
 }
 
 template <int NCB, int NRB>
 hipError_t launch_tsqr_mfma_ncb(bool bf16x3, int leaf_begin, int nleaves_cls, const int32_t* leaf_prob,
                                 const int32_t* leaf_idx, const ProbDesc* probs, int n, const float* Red, const double* d,
-                                const double* lam, float* slots, int* counters, float* RB, const QStore& qs,
+                                const double* lam, float* slots, float* RB, const QStore& qs,
                                 hipStream_t st) {
   // the plain leaves stream tiles of leaf_tile_rows rows, the leaves that store Q those of
   // leaf_tile_rows_keep (the stored Q's tile count per leaf)
@@ -813,17 +728,17 @@ hipError_t launch_tsqr_mfma_ncb(bool bf16x3, int leaf_begin, int nleaves_cls, co
   if (qs.qt != nullptr) {
     if (bf16x3)
       hipLaunchKernelGGL((k_tsqr_mfma_keep<NCB, NRBK, true>), dim3(grid), dim3(256), 0, st, leaf_begin, nleaves_cls,
-                         leaf_prob, leaf_idx, probs, n, Red, d, lam, slots, counters, RB, qs);
+                         leaf_prob, leaf_idx, probs, n, Red, d, lam, slots, RB, qs);
     else
       hipLaunchKernelGGL((k_tsqr_mfma_keep<NCB, NRBK, false>), dim3(grid), dim3(256), 0, st, leaf_begin, nleaves_cls,
-                         leaf_prob, leaf_idx, probs, n, Red, d, lam, slots, counters, RB, qs);
+                         leaf_prob, leaf_idx, probs, n, Red, d, lam, slots, RB, qs);
   } else {
     if (bf16x3)
       hipLaunchKernelGGL((k_tsqr_mfma<NCB, NRB, true>), dim3(grid), dim3(256), 0, st, leaf_begin, nleaves_cls,
-                         leaf_prob, leaf_idx, probs, n, Red, d, lam, slots, counters, RB);
+                         leaf_prob, leaf_idx, probs, n, Red, d, lam, slots, RB);
     else
       hipLaunchKernelGGL((k_tsqr_mfma<NCB, NRB, false>), dim3(grid), dim3(256), 0, st, leaf_begin, nleaves_cls,
-                         leaf_prob, leaf_idx, probs, n, Red, d, lam, slots, counters, RB);
+                         leaf_prob, leaf_idx, probs, n, Red, d, lam, slots, RB);
   }
   return hipGetLastError();
 }

@@ -1,25 +1,22 @@
 // Launch of the pipelined dense-part merge tree (see tsqr_tree.hpp), one instantiation per
-// column-block count up to kTreeMaxNCB = 8.
+// column-block count 1 .. 8.
 #include "qrk_launch.hpp"
 #include "tsqr_tree.hpp"
 
 namespace qrk {
 
-hipError_t launch_tsqr_tree(int ncb, const ProbDesc* probs, const int32_t* node_l, const int32_t* node_r,
-                            int nnodes, float* slots, int* flags, float* RB, int* status, const QStore& qs,
-                            hipStream_t st) {
-  if (nnodes < 1) return hipSuccess;
+hipError_t launch_tsqr_tree(int ncb, const ProbDesc* probs, const TreeNodes& tn, float* slots, int* flags, float* RB,
+                            int* status, const QStore& qs, hipStream_t st) {
+  if (tn.count < 1) return hipSuccess;
   switch (ncb) {
 #define QRK_TREE(N)                                                                                          \
   case N: {                                                                                                  \
     const int wpg = tree_waves(N, qs.qn != nullptr);                                                         \
-    const dim3 grid((unsigned)((nnodes + wpg - 1) / wpg)), blk(64 * wpg);                                    \
+    const dim3 grid((unsigned)((tn.count + wpg - 1) / wpg)), blk(64 * wpg);                                    \
     if (qs.qn)                                                                                               \
-      hipLaunchKernelGGL((k_tsqr_tree_keep<N>), grid, blk, 0, st, probs, node_l, node_r, nnodes, slots, flags, \
-                         RB, status, qs);                                                                    \
+      hipLaunchKernelGGL((k_tsqr_tree_keep<N>), grid, blk, 0, st, probs, tn, slots, flags, RB, status, qs);     \
     else                                                                                                     \
-      hipLaunchKernelGGL((k_tsqr_tree<N>), grid, blk, 0, st, probs, node_l, node_r, nnodes, slots, flags, RB,  \
-                         status);                                                                            \
+      hipLaunchKernelGGL((k_tsqr_tree<N>), grid, blk, 0, st, probs, tn, slots, flags, RB, status);              \
     break;                                                                                                   \
   }
     QRK_TREE(1) QRK_TREE(2) QRK_TREE(3) QRK_TREE(4) QRK_TREE(5) QRK_TREE(6) QRK_TREE(7) QRK_TREE(8)

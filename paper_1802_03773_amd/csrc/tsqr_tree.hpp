@@ -3,7 +3,7 @@
 // What is computed (QRkit Section 4.2): the triangle of QR([R_left; R_right]) at every inner
 // node of the tall-skinny QR's reduction tree, the root being R_B | c_B.
 //
-// Organisation.  The leaves (k_tsqr_mfma with the problem's tree_sep set) store their
+// Organisation.  The leaves (k_tsqr_mfma, k_tsqr_queue) store their
 // triangles and exit.  Here one wave per merge node works left-looking over column blocks of
 // 16.  Column block q is published in two parts, each with a flag of its own: the blocks above
 // the diagonal (block rows 0..q-1), which are final once the node's panels 0..q-1 have been
@@ -22,9 +22,8 @@
 // complete before storing the flag, the consumer polls the flag with device-scope loads and
 // only then issues the block's loads.
 //
-// Forward progress.  Nodes are numbered level by level from the leaves up, and the children
-// of a node are leaves or nodes with smaller numbers.  Wave w of the launch runs node w and
-// workgroups are dispatched in order, so a wave only waits for waves that were dispatched
+// Forward progress.  The node entries are in level order from the leaves up, and the children
+// of a node are leaves or earlier entries.  Wave w of the launch runs entry w and workgroups are dispatched in order, so a wave only waits for waves that were dispatched
 // before it or belong to its own workgroup.  Every wait is bounded: a flag not seen within the
 // bound sets the problem's ST_STALL status bit, and the wave still publishes every column
 // block so that no other wave waits on it.
@@ -137,12 +136,13 @@ __device__ __forceinline__ f4 tree_load_block(const float* src, int lane) {
   return __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, 0, kCoherent);
 }
 
-// One wave per inner node of the (single) problem's tree.  node_l / node_r: child references,
-// r >= 0 an inner node, r < 0 leaf -1 - r.  Leaf triangles are at slots 0 .. leaves-1 of the
+// One wave per inner node of the trees of every problem with NCB column blocks: wave w runs entry
+// tn.begin + w, node idx of problem prob with children l / r (>= 0 a node of the same problem, < 0 its
+// leaf -1 - r).  The entries are in level order over all the problems.  Leaf triangles are at slots 0 .. leaves-1 of the
 // problem, node outputs at slots leaves + node; flags[(node * NCB + q) * 2] marks column block
 // q of a node's output as published above the diagonal, flags[(node * NCB + q) * 2 + 1] its
-// diagonal block.  The root (the last node) writes R_B | c_B row-major.  KEEP (the stored Q):
-// node w's kept panels are written to qs.qn + qn0 + w * TreeKeep<NCB>::total at its end.
+// diagonal block.  A root (a problem's last node) writes R_B | c_B row-major.  KEEP (the stored Q):
+// node k's kept panels are written to qs.qn + qn0 + k * TreeKeep<NCB>::total at its end.
 // A node keeps its panels but the last one (no column block is left to apply that to), unless Q is
 // stored, which takes every panel from LDS.  Waves (nodes) per workgroup: four (150.5 KiB of LDS
 // at 8 column blocks), or three at 8 column blocks with the stored Q (46 KiB each).  Four matter
@@ -156,26 +156,27 @@ constexpr int tree_lds_floats() {
 }
 
 template <int NCB, bool KEEP>
-__device__ __forceinline__ void tsqr_tree_node(const ProbDesc* probs, const int32_t* node_l, const int32_t* node_r,
-                                               int nnodes, float* slots, int* flags, float* RBall, int* status,
-                                               const QStore& qs) {
+__device__ __forceinline__ void tsqr_tree_node(const ProbDesc* probs, const TreeNodes& tn, float* slots, int* flags,
+                                               float* RBall, int* status, const QStore& qs) {
   constexpr int WPG = tree_waves(NCB, KEEP);
   __shared__ float keep_all[WPG][tree_lds_floats<NCB, KEEP>()];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int node = blockIdx.x * WPG + wv;
-  if (node >= nnodes) return;
-  const ProbDesc& P = probs[0];
+  const int entry = blockIdx.x * WPG + wv;
+  if (entry >= tn.count) return;
+  const int pi = tn.prob[tn.begin + entry];
+  const int node = tn.idx[tn.begin + entry];
+  const int lref = tn.l[tn.begin + entry], rref = tn.r[tn.begin + entry];
+  const ProbDesc& P = probs[pi];
   const int L = P.L;
   const int nleaves = P.leaves;
   constexpr int SLOT = Tri<NCB>::count * 256;
   float* pslots = slots + P.slot0;
   int* pflags = flags + P.ctr0;
-  const int lref = node_l[node], rref = node_r[node];
   const float* lsrc = pslots + (int64_t)(lref >= 0 ? nleaves + lref : -1 - lref) * SLOT;
   const float* rsrc = pslots + (int64_t)(rref >= 0 ? nleaves + rref : -1 - rref) * SLOT;
   float* out = pslots + (int64_t)(nleaves + node) * SLOT;
-  const bool root = node == nnodes - 1;
+  const bool root = node == nleaves - 2;
   float* keep = keep_all[wv];
   const int g = lane >> 4;
   const int c = lane & 15;
@@ -259,27 +260,25 @@ __device__ __forceinline__ void tsqr_tree_node(const ProbDesc* probs, const int3
   });
   if constexpr (KEEP) {
     // the stored Q: this node's kept panels, as they are in LDS (TreeKeep layout)
-    float* dst = qs.qn + qs.qo[0].qn0 + (int64_t)node * TreeKeep<NCB>::total;
+    float* dst = qs.qn + qs.qo[pi].qn0 + (int64_t)node * TreeKeep<NCB>::total;
     for (int e = lane * 4; e < TreeKeep<NCB>::total; e += 256)
       *reinterpret_cast<f4*>(dst + e) = *reinterpret_cast<const f4*>(keep + e);
   }
-  if (stalled) set_status(status, ST_STALL);
+  if (stalled) set_status(status + pi, ST_STALL);
 }
 
 // The launch that stores Q is a kernel of its own with one more argument.
 template <int NCB>
 __global__ void __launch_bounds__(256)
-k_tsqr_tree(const ProbDesc* __restrict__ probs, const int32_t* __restrict__ node_l,
-            const int32_t* __restrict__ node_r, int nnodes, float* __restrict__ slots, int* __restrict__ flags,
+k_tsqr_tree(const ProbDesc* __restrict__ probs, TreeNodes tn, float* __restrict__ slots, int* __restrict__ flags,
             float* __restrict__ RBall, int* __restrict__ status) {
-  tsqr_tree_node<NCB, false>(probs, node_l, node_r, nnodes, slots, flags, RBall, status, QStore());
+  tsqr_tree_node<NCB, false>(probs, tn, slots, flags, RBall, status, QStore());
 }
 template <int NCB>
 __global__ void __launch_bounds__(256)
-k_tsqr_tree_keep(const ProbDesc* __restrict__ probs, const int32_t* __restrict__ node_l,
-                 const int32_t* __restrict__ node_r, int nnodes, float* __restrict__ slots, int* __restrict__ flags,
-                 float* __restrict__ RBall, int* __restrict__ status, const QStore qs) {
-  tsqr_tree_node<NCB, true>(probs, node_l, node_r, nnodes, slots, flags, RBall, status, qs);
+k_tsqr_tree_keep(const ProbDesc* __restrict__ probs, TreeNodes tn, float* __restrict__ slots,
+                 int* __restrict__ flags, float* __restrict__ RBall, int* __restrict__ status, const QStore qs) {
+  tsqr_tree_node<NCB, true>(probs, tn, slots, flags, RBall, status, qs);
 }
 
 }  // namespace qrk
