@@ -84,6 +84,8 @@ struct qrk_handle_s {
   // autotuner knobs (tune_cache.hpp): leaf queue on or off, refinement workgroups scale; nwg_cap
   // is the refinement workgroup capacity reserved at create (the count at the largest scale)
   int leaf_queue = 1;
+  bool queue_chosen = false;     // leaf_queue comes from the autotuner or its cache
+  bool use_queue = true;         // what a factor does: leaf_queue if chosen, else assign_leaves' rule on the rows
   double refine_scale = 1.0;
   int nwg_cap = 1;
   int widths = 1;                // float32 leaf classes of at most kQueueNCB column blocks present

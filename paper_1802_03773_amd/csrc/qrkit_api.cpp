@@ -116,7 +116,7 @@ qrk_status factor_ba(qrk_handle h, hipStream_t st, const double* lam_host = null
     // dense parts on the matrix cores: leaves and merge trees, one launch per column-block count
     float* slots = static_cast<float*>(h->slots);
     pr = prof_begin(h, 1, st);
-    if (launch_tsqr_mfma(h->mode == QRK_BF16X3, h->cls_begin, h->cls_count, h->queue_begin, h->leaf_queue != 0, h->cus,
+    if (launch_tsqr_mfma(h->mode == QRK_BF16X3, h->cls_begin, h->cls_count, h->queue_begin, h->use_queue, h->cus,
                          h->leaf_prob, h->leaf_idx, h->probs_d, h->n, Red, h->d, h->lam_ptr, slots,
                          h->nctr, h->counters + h->qhead_off, RB, qs, st) != hipSuccess)
       return QRK_EHIP;
@@ -368,6 +368,12 @@ qrk_status assign_leaves(qrk_handle h) {
     h->queue_begin = (int)lp.size();
     for (int c = kQueueNCB; c >= 1; --c)
       if (h->cls_count[c] > 0) h->queue_begin = std::min(h->queue_begin, h->cls_begin[c]);
+    // Without a tuned choice, batches of several widths run their leaves in the queue launch from 4,096
+    // rows a SIMD on, else in a launch per width.  The queue evens out the ends of the widths' launches
+    // but calls each width's body as a function.  Queue against launches, us a step: 0.4 M rows with 6
+    // or 30 columns 229 / 199, 1.1 M with 6, 30 or 90 1,007 / 915, 1.5 M with 0, 13 or 47 595 / 519,
+    // 2.2 M with 6, 30 or 90 1,676 / 1,663, 7.6 M 3,968 / 4,121, 12 M 5,807 / 5,959.
+    h->use_queue = h->queue_chosen ? h->leaf_queue != 0 : h->M >= 4096 * 4 * (int64_t)h->cus;
     // the leaf and node tables: one allocation, one copy
     const int64_t nn = (int64_t)np.size(), nleaf = (int64_t)lp.size(), nt = 2 * nleaf + 4 * nn;
     qrk_status s;
@@ -665,6 +671,7 @@ qrk_status create_ba(int32_t P, int32_t n, const int32_t* Kp, const int32_t* nBp
     if (tune_lookup(handle_tune_key(h), &tc)) {
       h->leaf_scale = tc.leaf_scale;
       h->leaf_queue = tc.leaf_queue;
+      h->queue_chosen = true;
       h->refine_scale = tc.refine_scale;
     }
     const double keep = h->refine_scale;
@@ -1215,7 +1222,8 @@ qrk_status qrk_autotune_blockangular(qrk_handle h, double* scale_host, void* str
   // refinement workgroups, each from the best of the previous ones
   TuneChoice best;
   best.leaf_scale = h->leaf_scale;
-  best.leaf_queue = h->leaf_queue;
+  best.leaf_queue = h->widths > 1 ? (h->use_queue ? 1 : 0) : h->leaf_queue;
+  h->queue_chosen = true;
   best.refine_scale = h->refine_scale;
   best.ms = 1e300;
   auto try_config = [&](double ls, int lq, double rs) {
