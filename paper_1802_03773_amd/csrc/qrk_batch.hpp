@@ -72,6 +72,7 @@ struct TreeNodes {
   const int32_t* idx = nullptr;
   const int32_t* l = nullptr;
   const int32_t* r = nullptr;
+  int* ticket = nullptr;  // counter of the workgroups that have started, cleared with the flags
 };
 
 // Stored Q of a problem's dense part (in an array of its own, so that the kernels without the

@@ -77,6 +77,22 @@ __device__ __forceinline__ void bqr_prologue(const BqrPrologue& pro) {
   if (threadIdx.x == 0 && pro.lam_out) *pro.lam_out = pro.lam_val;
 }
 
+// First node entry of a workgroup of a pipelined merge tree (WPG waves, an entry each; entries in
+// level order): workgroups are numbered as they start, by a counter, not by block index.  A node waits
+// for lower entries only, so whatever a wave waits for belongs to a workgroup that has started and
+// keeps its compute unit: the lowest unfinished entry never waits for a workgroup still to be placed.
+// Block indices do not give that.  The XCDs place their shares of a grid each at its own pace, so with
+// two such launches on two streams the waiting nodes of each could hold one XCD against the other's
+// children.  The count costs a memory round trip, about 1 us a launch.
+template <int WPG>
+__device__ __forceinline__ int tree_first_entry(int* ticket) {
+  if (gridDim.x == 1) return 0;  // the workgroup is placed as a whole
+  __shared__ int first;
+  if (threadIdx.x == 0) first = atomicAdd(ticket, 1);
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(first) * WPG;
+}
+
 // Flags between the nodes of a pipelined merge tree: flag 2 q + k of a node says that part k (0: above
 // the diagonal, 1: the diagonal block) of its column block q is published.  A look reads both parts'
 // flags of both children (fa, fb) in one device-scope load, a lane each, so a round trip to memory

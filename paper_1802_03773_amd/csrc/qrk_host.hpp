@@ -79,6 +79,7 @@ struct qrk_handle_s {
   int cls_begin[9] = {0};        // float32 leaves grouped by 16-column-block count, widest first
   int queue_begin = 0;           // first leaf of the persistent launch (classes 6 .. 1)
   int64_t qhead_off = 0;         // its queue head among the counters
+  int64_t ticket_off = 0;        // and the merge trees' tickets, one per column-block count (9)
   int cus = 256;                 // compute units of the device
   char arch[32] = {0};           // its architecture name (autotuner cache key)
   // autotuner knobs (tune_cache.hpp): leaf queue on or off, refinement workgroups scale; nwg_cap

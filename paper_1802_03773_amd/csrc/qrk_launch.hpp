@@ -33,7 +33,7 @@ hipError_t launch_blockqr_n(const int32_t* blk_list, int64_t begin, int64_t coun
 // Float64 tall-skinny QR on the matrix cores (tsqr_f64.hpp) of the problems with ncb column
 // blocks: their leaves (global leaves [leaf_begin, leaf_begin + count) of leaf_prob / leaf_idx), then
 // the inner nodes of their merge trees (entries [node_begin, node_begin + count), in level order
-// over all of them; flags cleared beforehand, two per node and column block).
+// over all of them; flags, two per node and column block, and the launch's ticket cleared beforehand).
 int tsqr64_slot_doubles(int L);
 int tsqr64_tile_rows(int ncb);
 hipError_t launch_tsqr64_leaves(int ncb, int leaf_begin, int count, const int32_t* leaf_prob, const int32_t* leaf_idx,
@@ -41,7 +41,7 @@ hipError_t launch_tsqr64_leaves(int ncb, int leaf_begin, int count, const int32_
                                 double* slots, double* RB, hipStream_t st);
 hipError_t launch_tsqr64_tree(int ncb, int node_begin, int count, const int32_t* node_prob, const int32_t* node_idx,
                               const int32_t* node_l, const int32_t* node_r, const ProbDesc* probs, double* slots,
-                              int* flags, double* RB, int* status, hipStream_t st);
+                              int* flags, int* ticket, double* RB, int* status, hipStream_t st);
 
 // Float32 tall-skinny QR on the matrix cores for a batch: the global leaves
 // [cls_begin[c], cls_begin[c] + cls_count[c]) are the leaves of the problems with c
@@ -55,7 +55,7 @@ int tsqr_mfma_slot_floats(int L);
 hipError_t launch_zero_ints(int* p, int64_t n, hipStream_t st);
 
 // Pipelined merge trees of the problems with ncb column blocks whose leaves stored their triangles:
-// one wave per inner node; flags are cleared by the factor call's first launch.
+// one wave per inner node; flags and tickets are cleared by the factor call's first launch.
 hipError_t launch_tsqr_tree(int ncb, const ProbDesc* probs, const TreeNodes& tn, float* slots, int* flags, float* RB,
                             int* status, const QStore& qs, hipStream_t st);
 // Leaves of classes 8 and 7 by their launches; the leaves from queue_begin on (classes

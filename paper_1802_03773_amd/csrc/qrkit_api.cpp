@@ -128,6 +128,7 @@ qrk_status factor_ba(qrk_handle h, hipStream_t st, const double* lam_host = null
       tn.idx = h->node_idx;
       tn.l = h->node_l;
       tn.r = h->node_r;
+      tn.ticket = h->counters + h->ticket_off + c;
       if (launch_tsqr_tree(c, h->probs_d, tn, slots, h->counters, RB, h->status, qs, st) != hipSuccess)
         return QRK_EHIP;
     }
@@ -147,7 +148,8 @@ qrk_status factor_ba(qrk_handle h, hipStream_t st, const double* lam_host = null
     pr = prof_begin(h, 2, st);
     for (int c = 8; c >= 1; --c)
       if (launch_tsqr64_tree(c, h->node_begin[c], h->node_count[c], h->node_prob, h->node_idx, h->node_l, h->node_r,
-                             h->probs_d, slots, h->counters, RB, h->status, st) != hipSuccess)
+                             h->probs_d, slots, h->counters, h->counters + h->ticket_off + c, RB, h->status,
+                             st) != hipSuccess)
         return QRK_EHIP;
     prof_end(h, pr, st);
   }
@@ -364,6 +366,8 @@ qrk_status assign_leaves(qrk_handle h) {
     h->q_u_n = std::max<int64_t>(qu, 1);
     h->qhead_off = ctr;  // the persistent leaf launch's queue head, cleared with the counters
     ctr += 1;
+    h->ticket_off = ctr;  // the merge trees' tickets, likewise
+    ctr += 9;
     h->nctr = ctr;
     h->queue_begin = (int)lp.size();
     for (int c = kQueueNCB; c >= 1; --c)

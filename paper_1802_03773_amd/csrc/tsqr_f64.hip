@@ -30,13 +30,13 @@ hipError_t launch_tsqr64_leaves(int ncb, int leaf_begin, int count, const int32_
 
 hipError_t launch_tsqr64_tree(int ncb, int node_begin, int count, const int32_t* node_prob, const int32_t* node_idx,
                               const int32_t* node_l, const int32_t* node_r, const ProbDesc* probs, double* slots,
-                              int* flags, double* RB, int* status, hipStream_t st) {
+                              int* flags, int* ticket, double* RB, int* status, hipStream_t st) {
   if (count < 1) return hipSuccess;
   switch (ncb) {
 #define QRK_T64(N)                                                                                              \
   case N:                                                                                                       \
     return launch_tsqr64_tree_n<N>(node_begin, count, node_prob, node_idx, node_l, node_r, probs, slots, flags, \
-                                   RB, status, st);
+                                   ticket, RB, status, st);
     QRK_T64_EACH(QRK_T64)
 #undef QRK_T64
     default:

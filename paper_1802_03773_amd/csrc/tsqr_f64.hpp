@@ -448,22 +448,22 @@ __device__ __forceinline__ d4 tree_load64(const double* src, int lane) {
 // One wave per inner node of the trees of every problem with NCB column blocks: wave w runs node
 // entry node_begin + w, node node_idx of problem node_prob with children node_l / node_r (>= 0 a
 // node of the same problem, < 0 its leaf -1 - r).  The entries are in level order over all the
-// problems, so a node's children are leaves (the launch before) or entries of earlier waves, and
-// workgroups are dispatched in order: a wave waits only for waves dispatched before it or with
-// it.  Every wait is bounded; a timeout sets the problem's ST_STALL bit and the wave still
-// publishes every block.  Leaf triangles are at the problem's slots 0 .. leaves - 1, node outputs
+// problems and workgroups take them as they start (tree_first_entry), so a node's children are
+// leaves (the launch before) or entries of waves that have started.  Every wait is bounded all the
+// same; a timeout sets the problem's ST_STALL bit and the wave still publishes every block.  Leaf triangles are at the problem's slots 0 .. leaves - 1, node outputs
 // at slots leaves + node; flags[(node NCB + q) 2 + k] at the problem's ctr0 (cleared by the factor
 // call's first launch): k = 0 the blocks above the diagonal of column block q, 1 its diagonal block.
 template <int NCB>
 __global__ void __launch_bounds__(64 * tree_waves_f64(NCB))
 k_tsqr64_tree(int node_begin, int nnodes, const int32_t* __restrict__ node_prob, const int32_t* __restrict__ node_idx,
               const int32_t* __restrict__ node_l, const int32_t* __restrict__ node_r,
-              const ProbDesc* __restrict__ probs, double* slots, int* flags, double* __restrict__ RBall, int* status) {
+              const ProbDesc* __restrict__ probs, double* slots, int* flags, int* ticket, double* __restrict__ RBall,
+              int* status) {
   constexpr int WPG = tree_waves_f64(NCB);
   __shared__ double keep_all[WPG][TreeKeep64<NCB>::total];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int entry = blockIdx.x * WPG + wv;
+  const int entry = tree_first_entry<WPG>(ticket) + wv;
   if (entry >= nnodes) return;
   const int pi = node_prob[node_begin + entry];
   const int node = node_idx[node_begin + entry];
@@ -590,7 +590,7 @@ hipError_t launch_tsqr64_leaf_n(int leaf_begin, int count, const int32_t* leaf_p
 template <int NCB>
 hipError_t launch_tsqr64_tree_n(int node_begin, int count, const int32_t* node_prob, const int32_t* node_idx,
                                 const int32_t* node_l, const int32_t* node_r, const ProbDesc* probs, double* slots,
-                                int* flags, double* RB, int* status, hipStream_t st);
+                                int* flags, int* ticket, double* RB, int* status, hipStream_t st);
 
 // The launches of one column-block count (one translation unit each, tsqr_f64_<N>.hip).
 #define QRK_TSQR64_INST(NCB)                                                                                     \
@@ -606,11 +606,12 @@ hipError_t launch_tsqr64_tree_n(int node_begin, int count, const int32_t* node_p
   template <>                                                                                                    \
   hipError_t launch_tsqr64_tree_n<NCB>(int node_begin, int count, const int32_t* node_prob,                      \
                                        const int32_t* node_idx, const int32_t* node_l, const int32_t* node_r,    \
-                                       const ProbDesc* probs, double* slots, int* flags, double* RB,             \
-                                       int* status, hipStream_t st) {                                            \
+                                       const ProbDesc* probs, double* slots, int* flags, int* ticket,            \
+                                       double* RB, int* status, hipStream_t st) {                                \
     constexpr int W = tree_waves_f64(NCB);                                                                       \
     hipLaunchKernelGGL((k_tsqr64_tree<NCB>), dim3((unsigned)((count + W - 1) / W)), dim3(64 * W), 0, st,         \
-                       node_begin, count, node_prob, node_idx, node_l, node_r, probs, slots, flags, RB, status); \
+                       node_begin, count, node_prob, node_idx, node_l, node_r, probs, slots, flags, ticket, RB,  \
+                       status);                                                                                  \
     return hipGetLastError();                                                                                    \
   }
 

@@ -22,11 +22,12 @@
 // complete before storing the flag, the consumer polls the flag with device-scope loads and
 // only then issues the block's loads.
 //
-// Forward progress.  The node entries are in level order from the leaves up, and the children
-// of a node are leaves or earlier entries.  Wave w of the launch runs entry w and workgroups are dispatched in order, so a wave only waits for waves that were dispatched
-// before it or belong to its own workgroup.  Every wait is bounded: a flag not seen within the
-// bound sets the problem's ST_STALL status bit, and the wave still publishes every column
-// block so that no other wave waits on it.
+// Forward progress.  The node entries are in level order from the leaves up, and the children of a
+// node are leaves or earlier entries.  Workgroups take their entries in the order in which they
+// start (tree_first_entry), so a wave only waits for waves that have started, whatever else runs on
+// the GPU.  Every wait is bounded all the same: a flag not seen within the bound sets the problem's
+// ST_STALL status bit, and the wave still publishes every column block so that no other wave waits on
+// it.
 //
 // The panel factorisation and the compact-WY application are those of merge_tile (same
 // reflector sign, scales, T recurrence and layouts), split so that a panel's reflectors can be
@@ -162,7 +163,7 @@ __device__ __forceinline__ void tsqr_tree_node(const ProbDesc* probs, const Tree
   __shared__ float keep_all[WPG][tree_lds_floats<NCB, KEEP>()];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int entry = blockIdx.x * WPG + wv;
+  const int entry = tree_first_entry<WPG>(tn.ticket) + wv;
   if (entry >= tn.count) return;
   const int pi = tn.prob[tn.begin + entry];
   const int node = tn.idx[tn.begin + entry];
