@@ -136,15 +136,22 @@ template <>
 struct BsBits<double> {
   typedef uint64_t type;
 };
+// The smallest normal number; twice its root, from which on a pivot keeps every squared norm normal; and
+// the power of two by which a rotation's two inputs are multiplied when the sum of their squares is
+// not: no square overflows or is subnormal then.
 template <typename T>
 struct BsTiny;
 template <>
 struct BsTiny<float> {
   static constexpr float value = 0x1p-126f;
+  static constexpr float pivot = 0x1p-62f;
+  static constexpr float up = 0x1p100f;
 };
 template <>
 struct BsTiny<double> {
   static constexpr double value = 0x1p-1022;
+  static constexpr double pivot = 0x1p-510;
+  static constexpr double up = 0x1p700;
 };
 
 // c - a b into a register of its own: the row moves down one register at every step, and with the
@@ -261,6 +268,13 @@ k_bgivens_s(int P, int64_t M, int64_t N, const int32_t* __restrict__ row_start, 
       }
     }
   };
+  // Wide bands: do all pivots start high enough for every squared norm to be normal (they only grow)?
+  // Else (no damping, or tiny values) each step looks at its norms.
+  bool low = false;
+  if constexpr (W > 15) {
+    for (int64_t j = lane; j < N; j += RING) low = low || (T)(sl * dd[j]) < BsTiny<T>::pivot;
+    low = __ballot(low) != 0;
+  }
   fetch(0);
   stage(0);
   fetch(1);
@@ -299,8 +313,9 @@ k_bgivens_s(int P, int64_t M, int64_t N, const int32_t* __restrict__ row_start, 
     if constexpr (FULL * V <= W + 1) sn = *reinterpret_cast<const int32_t*>(src + W + 1);
   };
   // damping values of the lanes' next rows: block s / RING of columns is current, the lanes that
-  // retire in it take their row of the next block
-  auto load_d = [&](int64_t col) -> double { return col < N ? dd[col] : 0.0; };
+  // retire in it take their row of the next block (past the last column the last one's, so that no
+  // lane divides by zero)
+  auto load_d = [&](int64_t col) -> double { return dd[col < N ? col : N - 1]; };
   Rw[0] = (T)(sl * load_d(lane));
   T dnext = (T)(sl * load_d((int64_t)RING + lane));
   double dload = load_d((int64_t)2 * RING + lane);  // converted when it is needed
@@ -375,17 +390,26 @@ k_bgivens_s(int P, int64_t M, int64_t N, const int32_t* __restrict__ row_start, 
     // Every lane rotates its two rows.  With cs = a / r, sn = x_0 / r and tn = sn / (1 + cs) = x_0 / (r
     // + a), the rotation (R, x) -> (cs R + sn x, cs x - sn R) is three shears, three FMAs a column:
     // u = R + tn x, x' = x - sn u, R' = u + tn x'.  a >= 0, so tn <= 1.  Lanes whose row is spent or
-    // not there (x_0 = 0) keep both.  A squared norm below the smallest normal number rotates
-    // nothing; NaN does.
-    const T a = Rw[0];
-    const T q0 = fma(x[0], x[0], a * a);
-    const bool none = q0 < BsTiny<T>::value;
-    const T x0 = none ? T(0) : x[0];
-    const T q = none ? BsTiny<T>::value : q0;
+    // not there (x_0 = 0) keep both.  Up to W = 15 a squared norm below the smallest normal number
+    // rotates nothing (NaN does).  Above, sn and tn come from a and x_0 scaled up then, which changes
+    // neither; looking for such lanes at every step cost 8%, so only problems that can have them do.
+    T a = Rw[0], x0 = x[0];
+    T q = fma(x0, x0, a * a);
+    if constexpr (W <= 15) {
+      const bool none = q < BsTiny<T>::value;
+      x0 = none ? T(0) : x0;
+      q = none ? BsTiny<T>::value : q;
+    } else if (__builtin_expect(low, 0)) {
+      const T up = q < BsTiny<T>::value ? BsTiny<T>::up : T(1);
+      a *= up;
+      x0 *= up;
+      q = fma(x0, x0, a * a);
+      q = q < BsTiny<T>::value ? BsTiny<T>::value : q;  // a = x_0 = 0
+    }
     const T inv = bs_rsqrt(q);
     const T sn_ = x0 * inv;
     const T tn = x0 * bs_rcp(fma(q, inv, a));
-    Rw[0] = fma(tn, x0, a);  // a + x_0^2 / (r + a) = r
+    Rw[0] = fma(tn, W <= 15 ? x0 : x[0], Rw[0]);  // a + x_0^2 / (r + a) = r
 #pragma unroll
     for (int l = 1; l < W; ++l) {
       const T u = fma(tn, x[l], Rw[l]);

@@ -1,0 +1,34 @@
+"""Values whose squares are below the smallest normal number: a rotation of the wide bands' Givens QR still
+rotates.  The instance is one of ordinary values with J and d multiplied by a power of two, so its step is
+that instance's divided by it, exactly.  Bounds of the other banded tests (1e-5 float32 unrefined,
+1e-10 refined, 1e-11 float64)."""
+import numpy as np
+import pytest
+
+from oracle import banded
+from tests.gpu_util import log, p_err
+from workloads import generators as gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,k", [(np.float32, -66), (np.float32, -100), (np.float64, -518), (np.float64, -1000)])
+@pytest.mark.parametrize("lam", [1e-2, 0.0])
+@pytest.mark.parametrize("w", [16, 24, 31])
+def test_banded(w, dtype, k, lam):
+    import torch
+    from paper_1802_03773_amd import BandedSolver
+    inst = gen.make_banded(70 + w, N=90, w=w, lam=lam, dtype=dtype)
+    p_ref = banded.reference_solution(inst)[0]
+    s = 2.0 ** k
+    vals = (inst.vals * dtype(s)).astype(dtype)
+    assert np.array_equal(vals.astype(np.float64) / s, inst.vals.astype(np.float64))
+    dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (inst.row_start, vals, inst.b, inst.d * s)]
+    solver = BandedSolver(inst.M, inst.N, w, dtype=np.dtype(dtype).name)
+    solver.factor(*dev, inst.lam)
+    # the refinement's lam d^2 needs d^2 in float64
+    for sweeps, tol in ((0, 1e-11),) if dtype == np.float64 else ((0, 1e-5), (2, 1e-10)):
+        p = solver.solve(sweeps=sweeps).cpu().numpy() * s
+        log(f"tiny values w={w} {np.dtype(dtype).name} 2^{k} sweeps={sweeps}: {p_err(p, p_ref, inst.d):.2e}")
+        assert solver.status()[0] == 0
+        assert p_err(p, p_ref, inst.d) <= tol
