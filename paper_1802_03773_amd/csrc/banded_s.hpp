@@ -272,7 +272,7 @@ k_bgivens_s(int P, int64_t M, int64_t N, const int32_t* __restrict__ row_start, 
   // Else (no damping, or tiny values) each step looks at its norms.
   bool low = false;
   if constexpr (W > 15) {
-    for (int64_t j = lane; j < N; j += RING) low = low || (T)(sl * dd[j]) < BsTiny<T>::pivot;
+    for (int64_t j = lane; j < N; j += RING) low = low || (T)(sl * fabs(dd[j])) < BsTiny<T>::pivot;
     low = __ballot(low) != 0;
   }
   fetch(0);
@@ -314,8 +314,8 @@ k_bgivens_s(int P, int64_t M, int64_t N, const int32_t* __restrict__ row_start, 
   };
   // damping values of the lanes' next rows: block s / RING of columns is current, the lanes that
   // retire in it take their row of the next block (past the last column the last one's, so that no
-  // lane divides by zero)
-  auto load_d = [&](int64_t col) -> double { return dd[col < N ? col : N - 1]; };
+  // lane divides by zero).  Their size: the rotation needs pivots >= 0, and a row's sign is free.
+  auto load_d = [&](int64_t col) -> double { return fabs(dd[col < N ? col : N - 1]); };
   Rw[0] = (T)(sl * load_d(lane));
   T dnext = (T)(sl * load_d((int64_t)RING + lane));
   double dload = load_d((int64_t)2 * RING + lane);  // converted when it is needed
