@@ -122,7 +122,7 @@ __device__ __forceinline__ double rows_from64(double x, int c) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// sqrt(q) and 1 / sqrt(q) for normal q > 0: the hardware estimate (about 24 bits) and two
+// sqrt(q) and 1 / sqrt(q) for q > 0 (a subnormal one too: 1 / sqrt(q) < 2^537): the hardware estimate (about 24 bits) and two
 // Goldschmidt steps, then one correction of the root.  1 / t: the estimate and two Newton steps.
 __device__ __forceinline__ void sqrt_rsqrt64(double q, double& root, double& inv) {
   const double y = __builtin_amdgcn_rsq(q);
@@ -143,9 +143,9 @@ __device__ __forceinline__ double rcp64(double t) {
 }
 
 // Householder factorisation of one 16-column panel [Rd; X[0..RBN-1]] with the compact-WY factor T
-// built alongside: the steps and signs of panel_factor in tsqr_mfma.hpp.  A squared column norm
-// below the smallest normal double counts as zero (identity reflector); NaN takes the reflection,
-// so that it reaches R.  Column 0 reads tile values that the matrix cores may have just written,
+// built alongside: the steps and signs of panel_factor in tsqr_mfma.hpp.  A zero squared column norm
+// gives the identity reflector (a subnormal one reflects, to the digits that it has); NaN takes
+// the reflection, so that it reaches R.  Column 0 reads tile values that the matrix cores may have just written,
 // so its passes are compiler-generated code (which tracks that hazard), the others the fused groups.
 template <int RBN>
 __device__ __forceinline__ void panel_factor64(d4& Rd, d4 (&X)[RBN], double (&trow)[16], double& sc, int lane) {
@@ -173,7 +173,7 @@ __device__ __forceinline__ void panel_factor64(d4& Rd, d4 (&X)[RBN], double (&tr
     const double gram = sum_rows4_64(p0 + p1);  // x_j^T x_c
     const double sigma = row_bcast64<j>(gram);
     const double alpha = read_lane64(Rd[j >> 2], (j & 3) * 16 + j);
-    const bool refl = !(sigma < 0x1p-1022);
+    const bool refl = !(sigma == 0.0);
     double nrm, rinv;
     sqrt_rsqrt64(fma(alpha, alpha, sigma), nrm, rinv);
     const double bneg = alpha >= 0.0 ? -nrm : nrm;

@@ -1,12 +1,13 @@
 """Values whose squares are below the smallest normal number: a rotation of the wide bands' Givens QR still
-rotates.  The instance is one of ordinary values with J and d multiplied by a power of two, so its step is
-that instance's divided by it, exactly.  Bounds of the other banded tests (1e-5 float32 unrefined,
-1e-10 refined, 1e-11 float64)."""
+rotates, a reflector of the float64 dense part still reflects.  The instance is one of ordinary values with
+J and d (the dense columns and their d) multiplied by a power of two, so its step is that instance's
+divided by it, exactly.  Bounds of the other tests of these paths (1e-5 float32 unrefined, 1e-10 refined, 1e-11
+float64: the dense part's squares of about 2^-1032 keep 42 bits, and their sums more)."""
 import numpy as np
 import pytest
 
-from oracle import banded
-from tests.gpu_util import log, p_err
+from oracle import banded, refine
+from tests.gpu_util import log, p_err, to_device
 from workloads import generators as gen
 
 pytestmark = pytest.mark.gpu
@@ -32,3 +33,23 @@ def test_banded(w, dtype, k, lam):
         log(f"tiny values w={w} {np.dtype(dtype).name} 2^{k} sweeps={sweeps}: {p_err(p, p_ref, inst.d):.2e}")
         assert solver.status()[0] == 0
         assert p_err(p, p_ref, inst.d) <= tol
+
+
+@pytest.mark.parametrize("nB", [5, 20, 60, 90, 120])
+@pytest.mark.parametrize("leaves", [0, 1])
+def test_dense_part_f64(nB, leaves):
+    from paper_1802_03773_amd import BlockAngularSolver
+    inst = gen.make_blockangular(200 + nB, K=120, m=8, n=3, nB=nB, lam=1e-2, dtype=np.float64)
+    p_ref, _ = refine.reference_solution(inst)
+    s, k = 2.0 ** -516, 3 * inst.K
+    A, B, b, dev_d = to_device(inst)
+    B *= s
+    dev_d[k:] *= s
+    solver = BlockAngularSolver(inst.row_off, inst.n, inst.nB, dtype="float64")
+    solver.set_tsqr_shape(leaves, 0)
+    solver.factor(A, B, b, dev_d, inst.lam)
+    p = solver.solve(sweeps=0).cpu().numpy()
+    p[k:] *= s
+    log(f"tiny dense part nB={nB} leaves={leaves}: {p_err(p, p_ref, inst.d):.2e}")
+    assert solver.status()[0] == 0
+    assert p_err(p, p_ref, inst.d) <= 1e-11
