@@ -147,13 +147,18 @@ __device__ __forceinline__ double rcp64(double t) {
 // gives the identity reflector (a subnormal one reflects, to the digits that it has); NaN takes
 // the reflection, so that it reaches R.  Column 0 reads tile values that the matrix cores may have just written,
 // so its passes are compiler-generated code (which tracks that hazard), the others the fused groups.
-template <int RBN>
-__device__ __forceinline__ void panel_factor64(d4& Rd, d4 (&X)[RBN], double (&trow)[16], double& sc, int lane) {
+// ONLY: the panel is the whole matrix, of ncol <= 16 columns: the columns past them are left alone and
+// T is not built, since there is nothing to apply it to (90,000 rows, one column: factor 78 -> 41 us,
+// and 46 with the kernel before the matrix cores, which worked column by column).
+template <int RBN, bool ONLY = false>
+__device__ __forceinline__ void panel_factor64(d4& Rd, d4 (&X)[RBN], double (&trow)[16], double& sc, int lane,
+                                               int ncol = 16) {
   const int g = lane >> 4;
   const int c = lane & 15;
   sc = 0.0;
   static_for<0, 16>([&](auto JJ) {
     constexpr int j = decltype(JJ)::value;
+    if (ONLY && j >= ncol) return;
     const double rrow = rows_from64<(j & 3)>(Rd[j >> 2], c);  // R's row j in every row of the wave
     double p0 = 0.0, p1 = 0.0;
     if constexpr (j == 0) {
@@ -193,6 +198,7 @@ __device__ __forceinline__ void panel_factor64(d4& Rd, d4 (&X)[RBN], double (&tr
       for (int rb = 0; rb < RBN; ++rb) axpy4_64<j>(X[rb], nf);
     }
     if (g == (j & 3)) Rd[j >> 2] = (c > j) ? Rd[j >> 2] - s : (c == j ? beta : Rd[j >> 2]);
+    if constexpr (ONLY) return;
     const double gk = sc * pd;  // at lane k < j: w_k^T w_j
     double t = 0.0;
     static_for<0, j>([&](auto KK) {
@@ -261,11 +267,11 @@ struct Wy64 {
   }
 };
 
-// Merge the dense tile X (NRB block rows) into the running triangle R; the block rows from RL on
+// Merge the dense tile X (NRB block rows, L columns) into the running triangle R; the block rows from RL on
 // are in LDS at rl (block t at (t - first) * 256, lane-major).
 template <int NCB, int NRB, int RL>
 __device__ __forceinline__ void merge_tile64(d4 (&R)[Tri64<NCB>::count], d4 (&X)[NRB][NCB], double* __restrict__ lds,
-                                             double* __restrict__ rl, int lane) {
+                                             double* __restrict__ rl, int lane, int L) {
   constexpr int first = Tri64<NCB>::idx(RL, RL);
   auto tri = [&](int t) -> d4* { return reinterpret_cast<d4*>(rl + (t - first) * 256 + lane * 4); };
   static_for<0, NCB>([&](auto PP) {
@@ -276,10 +282,10 @@ __device__ __forceinline__ void merge_tile64(d4 (&R)[Tri64<NCB>::count], d4 (&X)
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) Xp[rb] = X[rb][P];
     if constexpr (P < RL) {
-      panel_factor64<NRB>(R[rp], Xp, trow, sc, lane);
+      panel_factor64<NRB, NCB == 1>(R[rp], Xp, trow, sc, lane, L);
     } else {
       d4 Rd = *tri(rp);
-      panel_factor64<NRB>(Rd, Xp, trow, sc, lane);
+      panel_factor64<NRB, NCB == 1>(Rd, Xp, trow, sc, lane, L);
       *tri(rp) = Rd;
     }
     if constexpr (P + 1 < NCB) {
@@ -382,7 +388,7 @@ k_tsqr64_leaf(int leaf_begin, int nleaves_cls, const int32_t* __restrict__ leaf_
         }
       }
     __builtin_amdgcn_sched_barrier(0);
-    merge_tile64<NCB, NRB, RL>(R, X, stage_all[wv], rl, lane);
+    merge_tile64<NCB, NRB, RL>(R, X, stage_all[wv], rl, lane, L);
   }
 #pragma unroll
   for (int t = first; t < NT; ++t) R[t] = *reinterpret_cast<const d4*>(rl + (t - first) * 256 + lane * 4);
@@ -557,7 +563,7 @@ k_tsqr64_tree(int node_begin, int nnodes, const int32_t* __restrict__ node_prob,
       d4 Xp[q + 1];
 #pragma unroll
       for (int rb = 0; rb <= q; ++rb) Xp[rb] = x[rb];
-      panel_factor64<q + 1>(a[q], Xp, trow, sc, lane);
+      panel_factor64<q + 1, NCB == 1>(a[q], Xp, trow, sc, lane, L);
       if constexpr (q + 1 < NCB) panel_keep64<q + 1>(keep + TreeKeep64<NCB>::off(q), trow, sc, Xp, lane);
     }
     if (root) {
