@@ -257,9 +257,9 @@ int64_t tree_level_slots(int64_t leaves) {
 
 // Dense-part leaves of every problem (single waves).  float32: per 16-column-block class c the
 // default is about max(a tile, rows_c / 4096) rows per leaf (rows_c: the class's reduced plus
-// damping rows; 128 rows in batches),
-// scaled by leaf_scale; float64: a tile of the class, or more in whole tiles so that a
-// class's leaves are about one round of waves.  At most 1024 leaves per problem; a single-problem
+// damping rows), in batches of 8 blocks whole tiles; scaled by leaf_scale.  float64: a tile of the class, or
+// more in whole tiles so that a class's leaves are about one round of waves.  At most 1024 leaves
+// per problem; a single-problem
 // handle may fix the count (h->leaves > 0).  Leaves and merge nodes are listed class by class for
 // the per-class launches, and each problem's merge tree gets the slots and the flags it needs.
 // Every tree is a launch of its own, pipelined over column blocks.  Merging a float32 batch's
@@ -283,7 +283,14 @@ qrk_status assign_leaves(qrk_handle h) {
         const int tile = tsqr64_tile_rows(c);
         per = tile * std::max(tile < 64 ? 96.0 / tile : 1.0, std::ceil(rows_cls[c] / (4.0 * h->cus * tile)));
       } else {
-        per = std::max(P == 1 ? (double)leaf_tile_rows(c) : 128.0, rows_cls[c] / 4096.0) * h->leaf_scale;
+        // batches of 8 blocks: 96-row tiles, and leaves of 128 rows ran two for little more than one's
+        // rows.  Whole tiles, of one round of waves where a tile each is more than that (us a step,
+        // 128-row leaves / tile each / whole tiles: 16 x 600 rows 246 / 194 / 194, 16 x 7,000 rows 317 /
+        // 384 / 319, 64 x 7,000 rows 1,042 / 1,053 / 634; BF16x3, 112 columns)
+        const int tile = leaf_tile_rows(c);
+        per = P > 1 && tile != 128 ? tile * std::ceil(rows_cls[c] / (4.0 * h->cus * tile))
+                                   : std::max((double)tile, rows_cls[c] / 4096.0);
+        per *= h->leaf_scale;
       }
       const int64_t def = std::max<int64_t>(
           1, std::min<int64_t>((int64_t)std::ceil((double)(D.M + D.nB) / std::max(per, 1.0)), 1024));
