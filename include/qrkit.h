@@ -435,9 +435,10 @@ qrk_status qrk_set_tsqr_shape(qrk_handle h, int32_t leaves, int32_t fanin);
  *   the number of refinement workgroups (1/2, 1 or 2 times the default).  The handle is left
  *   factored with the chosen shape.  The choice is remembered in the process, and in the
  *   cache file when one is set (qrk_tune_cache_file), under a key of the device architecture,
- *   dtype, mode, block width, widest dense part, number of dense-part widths, and the problem
- *   and row counts rounded up to powers of two; a handle created later for a matching key
- *   starts from it.  *scale_host [host, may be NULL] receives the chosen leaf scale.  Like
+ *   dtype, mode, block width, widest dense part, number of dense-part widths, the problem
+ *   and row counts rounded up to powers of two, and the generation of the library's kernels; a
+ *   handle created later for a matching key starts from it (choices timed with kernels of
+ *   another generation are not used).  *scale_host [host, may be NULL] receives the chosen leaf scale.  Like
  *   qrk_set_tsqr_shape it may rewrite the leaf and refinement tables, so an LM driver graph
  *   captured on this handle is captured again at its next qrk_lm_run.  QRK_EINVAL before any
  *   factor call.

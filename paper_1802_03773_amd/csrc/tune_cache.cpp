@@ -105,9 +105,9 @@ void check_env_locked() {
 
 std::string tune_key(const char* arch, int dtype, int mode, int P, int n, int64_t rows, int max_L, int widths) {
   char buf[160];
-  std::snprintf(buf, sizeof(buf), "%s/%s/%s/P%lld/n%d/rows%lld/L%d/w%d", arch, dtype == 0 ? "f32" : "f64",
+  std::snprintf(buf, sizeof(buf), "%s/%s/%s/P%lld/n%d/rows%lld/L%d/w%d/g%d", arch, dtype == 0 ? "f32" : "f64",
                 mode == 0 ? "plain" : "bf16x3", (long long)(P <= 8 ? P : pow2_bucket(P)), n,
-                (long long)pow2_bucket(rows > 0 ? rows : 1), max_L, widths);
+                (long long)pow2_bucket(rows > 0 ? rows : 1), max_L, widths, kTuneGeneration);
   return buf;
 }
 

@@ -17,7 +17,13 @@ struct TuneChoice {
   double ms = 0.0;            // the measured factor + one-sweep solve time of the choice
 };
 
-// "arch/dtype/mode/P/n/rows/L/widths" with P and the row count bucketed by powers of two.
+// Generation of the kernels that the knobs were timed with; raised when a change to the dense-part leaves,
+// the merge trees or the refinement moves what a knob is worth or what it multiplies.  2: merge trees of
+// batches in launches of their own, 96-row tiles at 8 column blocks.
+constexpr int kTuneGeneration = 2;
+
+// "arch/dtype/mode/P/n/rows/L/widths/generation" with P and the row count bucketed by powers of two.
+// Entries of another generation stay in the file and match no handle.
 std::string tune_key(const char* arch, int dtype, int mode, int P, int n, int64_t rows, int max_L, int widths);
 bool tune_lookup(const std::string& key, TuneChoice* out);
 // Remembers the choice in the process and rewrites the cache file (when one is set); returns
