@@ -446,8 +446,9 @@ qrk_status qrk_set_tsqr_shape(qrk_handle h, int32_t leaves, int32_t fanin);
 qrk_status qrk_autotune_blockangular(qrk_handle h, double* scale_host, void* stream);
 
 /* The launch-shape knobs a block-angular handle uses (from qrk_autotune_blockangular, the cache,
- * or the defaults 1, 1, 1, with which a batch of several widths takes the leaf queue by its
- * row count); any pointer [host] may be NULL.  QRK_EINVAL for a banded handle. */
+ * or the defaults 1, 1, 1, except that a float32 batch of several widths of at most 6 column
+ * blocks takes the leaf queue by its row count: 0 where it runs a launch per width); any pointer
+ * [host] may be NULL.  QRK_EINVAL for a banded handle. */
 qrk_status qrk_tune_get(qrk_handle h, double* leaf_scale, int32_t* leaf_queue, double* refine_scale);
 
 /* Sets the autotuner's cache file [host path, NULL: none] for the process and loads the choices

@@ -1273,7 +1273,8 @@ qrk_status qrk_autotune_blockangular(qrk_handle h, double* scale_host, void* str
 qrk_status qrk_tune_get(qrk_handle h, double* leaf_scale, int32_t* leaf_queue, double* refine_scale) {
   if (!h || h->kind != KIND_BLOCKANGULAR) return QRK_EINVAL;
   if (leaf_scale) *leaf_scale = h->leaf_scale;
-  if (leaf_queue) *leaf_queue = h->leaf_queue;
+  // what a factor does: without a tuned choice the rows decide (assign_leaves)
+  if (leaf_queue) *leaf_queue = h->dtype == QRK_F32 && h->widths > 1 ? (h->use_queue ? 1 : 0) : h->leaf_queue;
   if (refine_scale) *refine_scale = h->refine_scale;
   return QRK_OK;
 }

@@ -65,3 +65,13 @@ def test_both_leaf_launches(problems, tmp_path, mode, queue):
                     at += inst.N
     finally:
         qrkit.set_tune_cache(None)
+
+
+def test_reported_choice_is_the_one_used():
+    """An untuned batch of several widths and few rows runs a launch per width, and says so; one width, or
+    float64, has no queue to choose."""
+    from paper_1802_03773_amd import BlockAngularBatch, qrkit
+    off = np.arange(0, 8 * 60 + 1, 8)
+    for nBs, dtype, queue in (((6, 30), "float32", 0), ((6, 6), "float32", 1), ((6, 30), "float64", 1)):
+        bt = BlockAngularBatch([30, 30], nBs, off, 1, dtype=dtype)
+        assert qrkit.tune_choice(bt) == {"leaf_scale": 1, "leaf_queue": queue, "refine_scale": 1}, (nBs, dtype)
