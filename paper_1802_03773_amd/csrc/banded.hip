@@ -134,8 +134,8 @@ k_band_first_row(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__
 // the two sums are added, so the result is deterministic.  The row ranges come from the
 // first-row table.  A workgroup covers 128 consecutive columns of one problem: the starts,
 // residuals and values of its rows (one contiguous range) are copied to LDS with coalesced
-// loads, eight per thread in flight, and each column then reads only LDS.  Ranges beyond the
-// LDS capacity read their rows from memory.  Bound by the loads in flight: with 256 columns and
+// loads, eight per thread in flight, and each column then reads only LDS; a range beyond the
+// LDS capacity goes in chunks.  Bound by the loads in flight: with 256 columns and
 // 53 KB of LDS a workgroup three fitted a CU, now five of twice the threads per column do.  Two
 // rows per column: 2,048 problems of N = 2,048, w = 12 265 -> 207 us; 200 of N = 1,000, w = 20
 // 75 -> 18 (the range of 256 columns did not fit LDS); one row per column, 500 of N = 1,000,
@@ -168,11 +168,20 @@ k_banded_jt(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__ row_
   const int64_t lo = row_at(c0 - w + 1);
   int64_t hi = row_at(c0 + kJtCols);
   hi = hi < lo ? lo : hi;
-  const int64_t n = hi - lo;
-  const bool staged = n <= CAP && n * w <= VCAP;
-  if (staged) {
-    const int64_t nv = n * w;
-    const T* Vlo = V + lo * w;
+  int64_t a = 0, e = 0;  // this column's rows
+  if (j < N) {
+    a = row_at(j - w + 1);
+    e = row_at(j + 1);
+    a = a < lo ? lo : a;
+    e = e > hi ? hi : e;
+  }
+  double acc = 0.0;
+  const int64_t chunk = CAP < VCAP / w ? CAP : VCAP / w;
+  for (int64_t cs = lo; cs < hi; cs += chunk) {
+    const int64_t ce = cs + chunk < hi ? cs + chunk : hi;
+    const int64_t n = ce - cs, nv = n * w;
+    if (cs > lo) __syncthreads();  // every column is done with the chunk before
+    const T* Vlo = V + cs * w;
     for (int64_t i0 = 0; i0 < nv; i0 += 256 * 8) {
       T buf[8];
 #pragma unroll
@@ -192,8 +201,8 @@ k_banded_jt(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__ row_
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int64_t i = i0 + u * 256 + threadIdx.x;
-        sb[u] = i < n ? (int32_t)band_start(rs, lo + i, N, w) : 0;
-        rb[u] = i < n ? rp[lo + i] : 0.0;
+        sb[u] = i < n ? (int32_t)band_start(rs, cs + i, N, w) : 0;
+        rb[u] = i < n ? rp[cs + i] : 0.0;
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -205,16 +214,12 @@ k_banded_jt(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__ row_
       }
     }
     __syncthreads();
-  }
-  if (j >= N) return;
-  int64_t a = row_at(j - w + 1), e = row_at(j + 1);
-  double acc = 0.0;
-  if (staged) {
-    a = a < lo ? lo : a;
-    e = e > hi ? hi : e;
-    // four rows per batch: their LDS reads are independent, the sum keeps row order
-    const int i1 = (int)(e - lo);
-    for (int i0 = (int)(a - lo) + half; i0 < i1; i0 += 8) {
+    // this thread's rows of the chunk (every other one from a + half), four per batch: their LDS reads
+    // are independent, the sum keeps row order
+    const int64_t first = a + half, from = first < cs ? cs + ((cs - first) & 1) : first;
+    const int i1 = (int)((e < ce ? e : ce) - cs);
+    for (int64_t ib = from - cs; ib < i1; ib += 8) {
+      const int i0 = (int)ib;
       int kk[4];
       double rr[4];
 #pragma unroll
@@ -234,15 +239,9 @@ k_banded_jt(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__ row_
       for (int u = 0; u < 4; ++u)
         if (i0 + 2 * u < i1 && kk[u] >= 0 && kk[u] < w) acc += (double)vv[u] * rr[u];
     }
-  } else {
-    for (int64_t i = a + half; i < e; i += 2) {
-      const int64_t k = j - band_start(rs, i, N, w);
-      if (k < 0 || k >= w) continue;
-      acc += (double)V[i * w + k] * rp[i];
-    }
   }
   acc += __shfl_xor(acc, 1, kWave);
-  if (half) return;
+  if (half || j >= N) return;
   const int64_t t = prob * N + j;
   const double dj = d[t];
   g[t] = acc - lamv[prob] * dj * dj * v[t];
