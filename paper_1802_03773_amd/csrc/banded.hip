@@ -129,52 +129,46 @@ k_band_first_row(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__
   for (int64_t c = c0; c <= c1; ++c) f[c] = (int32_t)i;
 }
 
-// g = J^T r - lam d^2 v (float64), two threads per column: column j of a problem collects the
-// rows whose start lies in [j - w + 1, j], one thread every other row of the range in order, and
-// the two sums are added, so the result is deterministic.  The row ranges come from the
-// first-row table.  A workgroup covers 128 consecutive columns of one problem: the starts,
+// g = J^T r - lam d^2 v (float64), TPC threads per column: column j of a problem collects the
+// rows whose start lies in [j - w + 1, j], thread h of it rows h, h + TPC, ... of the range in order,
+// and two threads' sums are added, so the result is deterministic.  The row ranges come from the
+// first-row table.  A workgroup covers 256 / TPC consecutive columns of one problem: the starts,
 // residuals and values of its rows (one contiguous range) are copied to LDS with coalesced
 // loads, eight per thread in flight, and each column then reads only LDS; a range beyond the
-// LDS capacity goes in chunks.  Bound by the loads in flight: with 256 columns and
-// 53 KB of LDS a workgroup three fitted a CU, now five of twice the threads per column do.  Two
-// rows per column: 2,048 problems of N = 2,048, w = 12 265 -> 207 us; 200 of N = 1,000, w = 20
-// 75 -> 18 (the range of 256 columns did not fit LDS); one row per column, 500 of N = 1,000,
-// w = 4 14.3 -> 15.9.
-constexpr int kJtCols = 128;  // columns of a workgroup
-template <typename T>
+// LDS capacity goes in chunks.  Bound by the loads in flight: with 256 columns and 53 KB of LDS a
+// workgroup three fit a CU, with 128 five of twice the threads per column.  Two rows per column: 2,048
+// problems of N = 2,048, w = 12 265 us with one thread, 207 with two.
+//
+// Columns of fewer than 8 values have no work for two threads, unless 256 columns a workgroup leave more of
+// the last one empty (jt_thin).  Solves of two sweeps, one thread / two, one row per column: 2,000
+// problems of N = 1,000 w = 1 394 / 410 us, w = 4 419 / 442, w = 7 454 / 463, w = 10 no difference; N = 300,
+// w = 4 166 / 160.
+inline bool jt_thin(int64_t M, int64_t N, int w) { return M * w < 8 * N && (N - 1) % 256 >= 128; }
+template <typename T, int TPC>
 __global__ void __launch_bounds__(256)
 k_banded_jt(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__ row_start, const int32_t* __restrict__ fr,
             const T* __restrict__ vals, const double* __restrict__ r, const double* __restrict__ d,
             const double* __restrict__ lamv, const double* __restrict__ v, double* __restrict__ g) {
-  constexpr int CAP = 576;                           // rows
-  constexpr int VCAP = 24576 / (int)sizeof(T);       // values
+  constexpr int COLS = 256 / TPC;
+  constexpr int CAP = TPC == 1 ? 1024 : 576;                             // rows of a chunk
+  constexpr int VCAP = (TPC == 1 ? 40960 : 24576) / (int)sizeof(T);      // and values
   __shared__ int32_t s_st[CAP];
   __shared__ double s_r[CAP];
   __shared__ T s_v[VCAP];
-  const int64_t nb = (N + kJtCols - 1) / kJtCols;
+  const int64_t nb = (N + COLS - 1) / COLS;
   const int64_t prob = blockIdx.x / nb;
-  const int64_t c0 = (int64_t)(blockIdx.x % nb) * kJtCols;
-  const int64_t j = c0 + (threadIdx.x >> 1);
-  const int half = threadIdx.x & 1;
+  const int64_t c0 = (int64_t)(blockIdx.x % nb) * COLS;
+  const int64_t j = c0 + threadIdx.x / TPC;
+  const int half = threadIdx.x & (TPC - 1);
   const int32_t* rs = row_start + prob * M;
   const int32_t* f = fr + prob * (N + 1);
   const double* rp = r + prob * M;
   const T* V = vals + prob * M * w;
-  auto row_at = [&](int64_t c) -> int64_t {  // table entry, clamped to [0, M]
-    c = c < 0 ? 0 : (c > N ? N : c);
-    const int64_t i = f[c];
-    return i < 0 ? 0 : (i > M ? M : i);
-  };
-  const int64_t lo = row_at(c0 - w + 1);
-  int64_t hi = row_at(c0 + kJtCols);
-  hi = hi < lo ? lo : hi;
-  int64_t a = 0, e = 0;  // this column's rows
-  if (j < N) {
-    a = row_at(j - w + 1);
-    e = row_at(j + 1);
-    a = a < lo ? lo : a;
-    e = e > hi ? hi : e;
-  }
+  auto entry = [&](int64_t c) -> int64_t { return f[c < 0 ? 0 : (c > N ? N : c)]; };
+  auto clamp = [](int64_t i, int64_t lo, int64_t hi) -> int64_t { return i < lo ? lo : (i > hi ? hi : i); };
+  const int64_t fa = entry(j - w + 1), fe = entry(j + 1);  // this column's rows, used when a chunk is staged
+  const int64_t lo = clamp(entry(c0 - w + 1), 0, M);
+  const int64_t hi = clamp(entry(c0 + COLS), lo, M);
   double acc = 0.0;
   const int64_t chunk = CAP < VCAP / w ? CAP : VCAP / w;
   for (int64_t cs = lo; cs < hi; cs += chunk) {
@@ -214,33 +208,35 @@ k_banded_jt(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__ row_
       }
     }
     __syncthreads();
-    // this thread's rows of the chunk (every other one from a + half), four per batch: their LDS reads
+    // this thread's rows of the chunk (every TPC-th one from a + half), a few per batch: their LDS reads
     // are independent, the sum keeps row order
-    const int64_t first = a + half, from = first < cs ? cs + ((cs - first) & 1) : first;
+    const int64_t a = clamp(fa, lo, hi), e = j < N ? clamp(fe, lo, hi) : a;
+    const int64_t first = a + half, from = first < cs ? cs + ((cs - first) & (TPC - 1)) : first;
     const int i1 = (int)((e < ce ? e : ce) - cs);
+    constexpr int U = 8 / TPC;
     for (int64_t ib = from - cs; ib < i1; ib += 8) {
       const int i0 = (int)ib;
-      int kk[4];
-      double rr[4];
+      int kk[U];
+      double rr[U];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = i0 + 2 * u < i1 ? i0 + 2 * u : i0;
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + TPC * u < i1 ? i0 + TPC * u : i0;
         kk[u] = (int)(j - s_st[i]);
         rr[u] = s_r[i];
       }
-      T vv[4];
+      T vv[U];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int i = i0 + 2 * u < i1 ? i0 + 2 * u : i0;
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + TPC * u < i1 ? i0 + TPC * u : i0;
         const int k = kk[u] < 0 ? 0 : (kk[u] >= w ? w - 1 : kk[u]);
         vv[u] = s_v[i * w + k];
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (i0 + 2 * u < i1 && kk[u] >= 0 && kk[u] < w) acc += (double)vv[u] * rr[u];
+      for (int u = 0; u < U; ++u)
+        if (i0 + TPC * u < i1 && kk[u] >= 0 && kk[u] < w) acc += (double)vv[u] * rr[u];
     }
   }
-  acc += __shfl_xor(acc, 1, kWave);
+  if constexpr (TPC == 2) acc += __shfl_xor(acc, 1, kWave);
   if (half || j >= N) return;
   const int64_t t = prob * N + j;
   const double dj = d[t];
@@ -339,9 +335,15 @@ template <typename T>
 hipError_t launch_banded_jt(int P, int64_t M, int64_t N, int w, const int32_t* row_start, const int32_t* fr,
                             const T* vals, const double* r, const double* d, const double* lam, const double* v,
                             double* g, hipStream_t st) {
-  const int64_t blocks = (int64_t)P * ((N + kJtCols - 1) / kJtCols);
-  hipLaunchKernelGGL((k_banded_jt<T>), dim3((unsigned)blocks), dim3(256), 0, st, P, M, N, w, row_start, fr, vals, r,
-                     d, lam, v, g);
+  const bool thin = jt_thin(M, N, w);
+  const int cols = thin ? 256 : 128;
+  const int64_t blocks = (int64_t)P * ((N + cols - 1) / cols);
+  if (thin)
+    hipLaunchKernelGGL((k_banded_jt<T, 1>), dim3((unsigned)blocks), dim3(256), 0, st, P, M, N, w, row_start, fr, vals,
+                       r, d, lam, v, g);
+  else
+    hipLaunchKernelGGL((k_banded_jt<T, 2>), dim3((unsigned)blocks), dim3(256), 0, st, P, M, N, w, row_start, fr, vals,
+                       r, d, lam, v, g);
   return hipGetLastError();
 }
 
