@@ -156,8 +156,10 @@ k_banded_jt(int P, int64_t M, int64_t N, int w, const int32_t* __restrict__ row_
   __shared__ double s_r[CAP];
   __shared__ T s_v[VCAP];
   const int64_t nb = (N + COLS - 1) / COLS;
-  const int64_t prob = blockIdx.x / nb;
-  const int64_t c0 = (int64_t)(blockIdx.x % nb) * COLS;
+  const int64_t wg = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;  // (a grid row holds fewer than 2^32 threads)
+  const int64_t prob = wg / nb;
+  if (prob >= P) return;
+  const int64_t c0 = wg % nb * COLS;
   const int64_t j = c0 + threadIdx.x / TPC;
   const int half = threadIdx.x & (TPC - 1);
   const int32_t* rs = row_start + prob * M;
@@ -338,11 +340,13 @@ hipError_t launch_banded_jt(int P, int64_t M, int64_t N, int w, const int32_t* r
   const bool thin = jt_thin(M, N, w);
   const int cols = thin ? 256 : 128;
   const int64_t blocks = (int64_t)P * ((N + cols - 1) / cols);
+  const int64_t gx = blocks < (1 << 22) ? blocks : 1 << 22;
+  const dim3 grid((unsigned)gx, (unsigned)((blocks + gx - 1) / gx));
   if (thin)
-    hipLaunchKernelGGL((k_banded_jt<T, 1>), dim3((unsigned)blocks), dim3(256), 0, st, P, M, N, w, row_start, fr, vals,
+    hipLaunchKernelGGL((k_banded_jt<T, 1>), grid, dim3(256), 0, st, P, M, N, w, row_start, fr, vals,
                        r, d, lam, v, g);
   else
-    hipLaunchKernelGGL((k_banded_jt<T, 2>), dim3((unsigned)blocks), dim3(256), 0, st, P, M, N, w, row_start, fr, vals,
+    hipLaunchKernelGGL((k_banded_jt<T, 2>), grid, dim3(256), 0, st, P, M, N, w, row_start, fr, vals,
                        r, d, lam, v, g);
   return hipGetLastError();
 }
