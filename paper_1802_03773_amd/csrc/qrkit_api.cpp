@@ -292,8 +292,9 @@ qrk_status assign_leaves(qrk_handle h) {
                                    : std::max((double)tile, rows_cls[c] / 4096.0);
         per *= h->leaf_scale;
       }
+      // (float64 leaves are counted by the rows they stream: the damping rows are the first one's start)
       const int64_t def = std::max<int64_t>(
-          1, std::min<int64_t>((int64_t)std::ceil((double)(D.M + D.nB) / std::max(per, 1.0)), 1024));
+          1, std::min<int64_t>((int64_t)std::ceil((double)(f64 ? D.M : D.M + D.nB) / std::max(per, 1.0)), 1024));
       D.leaves = (int)(h->leaves > 0 ? h->leaves : def);
       D.rows_per_leaf = std::max<int64_t>(1, ceil_div(D.M, D.leaves));
     }
@@ -349,7 +350,7 @@ qrk_status assign_leaves(qrk_handle h) {
       const int64_t tri = f64 ? tsqr64_slot_doubles(D.L) : tsqr_mfma_slot_floats(D.L);
       D.slot0 = slot;
       D.ctr0 = ctr;
-      slot += (2 * (int64_t)D.leaves - 1) * tri;
+      slot += 2 * (int64_t)(D.leaves - 1) * tri;  // leaves and inner nodes; the root (or a single leaf) stores none
       ctr += (int64_t)(D.leaves - 1) * ((D.L + 15) / 16) * 2;  // two flags per column block
     }
     // stored Q: tile panels of every leaf, node panels of the leaves - 1 merges, and the
