@@ -77,6 +77,14 @@ __device__ __forceinline__ void bqr_prologue(const BqrPrologue& pro) {
   if (threadIdx.x == 0 && pro.lam_out) *pro.lam_out = pro.lam_val;
 }
 
+// A copy of x that the compiler cannot identify with x (an empty asm on a register;
+// no memory is touched).  The permlane swaps need two distinct operands.
+__device__ __forceinline__ unsigned opaque_copy(unsigned x) {
+  unsigned y = x;
+  asm volatile("" : "+v"(y));
+  return y;
+}
+
 // First node entry of a workgroup of a pipelined merge tree (WPG waves, an entry each; entries in
 // level order): workgroups are numbered as they start, by a counter, not by block index.  A node waits
 // for lower entries only, so whatever a wave waits for belongs to a workgroup that has started and

@@ -46,8 +46,9 @@ hipError_t launch_tsqr64_tree(int ncb, int node_begin, int count, const int32_t*
 // Float32 tall-skinny QR on the matrix cores for a batch: the global leaves
 // [cls_begin[c], cls_begin[c] + cls_count[c]) are the leaves of the problems with c
 // 16-column blocks (leaf_prob / leaf_idx: problem and index within it); one launch per c.
-// Each problem's leaves merge pairwise in the same launch (its slots from slot0, counters
-// from ctr0; nctr counters in all, cleared here) and its root goes to RB + rboff.
+// Each leaf stores its triangle at its slot (from the problem's slot0) for launch_tsqr_tree; a
+// problem's single leaf goes to RB + rboff.  The flags, the queue head and the tickets (nctr ints in
+// all) are cleared by the factor call's first launch.
 // bf16x3: the trailing updates' two large products are formed as three bf16 products each
 // (hi hi' + hi lo' + lo hi', fp32 accumulation).
 int tsqr_mfma_slot_floats(int L);
@@ -63,9 +64,9 @@ hipError_t launch_tsqr_tree(int ncb, const ProbDesc* probs, const TreeNodes& tn,
 // that takes them from the device counter *qhead (cleared with the counters) when use_queue is
 // set and more than one of those classes is present, else by a launch per class.
 hipError_t launch_tsqr_mfma(bool bf16x3, const int* cls_begin, const int* cls_count, int queue_begin, bool use_queue,
-                            int cus,
-                            const int32_t* leaf_prob, const int32_t* leaf_idx, const ProbDesc* probs, int n,
-                            const float* Red, const double* d, const double* lam, float* slots, int64_t nctr, int* qhead, float* RB, const QStore& qs, hipStream_t st);
+                            int cus, const int32_t* leaf_prob, const int32_t* leaf_idx, const ProbDesc* probs, int n,
+                            const float* Red, const double* d, const double* lam, float* slots, int64_t nctr,
+                            int* qhead, float* RB, const QStore& qs, hipStream_t st);
 
 // R_B p_B = c_B for every problem (RB_p is L x L with c_B in column L-1, or c_B from cext,
 // laid out like p, when that is given); writes p_B.

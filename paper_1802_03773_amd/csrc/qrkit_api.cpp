@@ -384,7 +384,9 @@ qrk_status assign_leaves(qrk_handle h) {
     // rows a SIMD on, else in a launch per width.  The queue evens out the ends of the widths' launches
     // but calls each width's body as a function.  Queue against launches, us a step: 0.4 M rows with 6
     // or 30 columns 229 / 199, 1.1 M with 6, 30 or 90 1,007 / 915, 1.5 M with 0, 13 or 47 595 / 519,
-    // 2.2 M with 6, 30 or 90 1,676 / 1,663, 7.6 M 3,968 / 4,121, 12 M 5,807 / 5,959.
+    // 2.2 M with 6, 30 or 90 1,676 / 1,663, 7.6 M 3,968 / 4,121, 12 M 5,807 / 5,959.  Queue over launches
+    // around the line, five sets of widths: 2.75 M rows 0.97 to 1.04, 3.7 M 0.98 to 1.03, 5.0 M 0.97 to
+    // 1.02, 7.4 M 0.95 to 1.01; with 80% of the problems at 6 columns 1.08 at 3.7 M and 1.06 at 7.4 M.
     h->use_queue = h->queue_chosen ? h->leaf_queue != 0 : h->M >= 4096 * 4 * (int64_t)h->cus;
     // the leaf and node tables: one allocation, one copy
     const int64_t nn = (int64_t)np.size(), nleaf = (int64_t)lp.size(), nt = 2 * nleaf + 4 * nn;

@@ -17,8 +17,8 @@ namespace qrk {
 // folds, and each lane ends with one row's sum.  (Before, the chunk went through LDS transposed
 // and each row was summed by four lanes: 128 columns of p_B per lane, 64 registers, held one wave
 // less per SIMD.)  All sums run in a fixed order.  Bound: instruction issue and, in large problems, the
-// stream itself.  Refinement pass 1 of 50,000 blocks of 12 x 3 with 91 columns 71 -> 54 us (3.2 -> 4.2
-// TB/s), of 128 ragged problems with 6, 30 or 90 columns 1,670 -> 1,006 us; block solves there 275 -> 91
+// stream itself.  Refinement pass 1 of 50,000 blocks of 12 x 3 with 91 columns 71 -> 54 us (4.0 -> 5.3
+// TB/s of A, B, b and S|c), of 128 ragged problems with 6, 30 or 90 columns 1,670 -> 1,006 us; block solves there 275 -> 91
 // us (units of 64 / n blocks instead of packs of 64 rows, and one load for up to four rows).
 // ---------------------------------------------------------------------------------
 template <typename T, int CW>
@@ -83,11 +83,6 @@ __device__ __forceinline__ double dpp_into(double old, double x) {
   const int hi = __builtin_amdgcn_update_dpp((int)(unsigned)(o >> 32), (int)(unsigned)(v >> 32), CTRL, 0xF, BANK, false);
   return mk_double((unsigned)lo, (unsigned)hi);
 }
-__device__ __forceinline__ unsigned opaque_u(unsigned x) {
-  unsigned y = x;
-  asm volatile("" : "+v"(y));
-  return y;
-}
 // x, which with FRESH the compiler cannot identify with x: a chunk is then converted to double anew
 // for its second use, else the converted values (twice the registers) are kept from the first.  Kept
 // they cost registers up to the two waves per SIMD that pass 1's grid fills, and save conversions:
@@ -127,7 +122,7 @@ template <int ST>
 __device__ __forceinline__ double fold1(double a) {
   if constexpr (ST <= 1) {
     const uint64_t u = __builtin_bit_cast(uint64_t, a);
-    return fold2<ST>(a, mk_double(opaque_u((unsigned)u), opaque_u((unsigned)(u >> 32))), 0);
+    return fold2<ST>(a, mk_double(opaque_copy((unsigned)u), opaque_copy((unsigned)(u >> 32))), 0);
   } else {
     constexpr int ctrl = ST == 2 ? 0x140 : (ST == 3 ? 0x141 : (ST == 4 ? 0x4E : 0xB1));
     return a + dpp_into<ctrl, 0xF>(a, a);

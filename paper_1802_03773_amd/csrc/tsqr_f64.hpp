@@ -88,22 +88,17 @@ __device__ __forceinline__ void axpy4_64(d4& x, double f) {
   x = d4{x0, x1, x2, x3};
 }
 
-__device__ __forceinline__ unsigned opaque_u32(unsigned x) {
-  unsigned y = x;
-  asm volatile("" : "+v"(y));
-  return y;
-}
 // Sum over the wave's four 16-lane rows, the same bits in every lane (the permlane swaps of
 // sum_rows4 in tsqr_mfma.hpp, on the two halves of a double).
 __device__ __forceinline__ double sum_rows4_64(double x) {
   uint64_t u = __builtin_bit_cast(uint64_t, x);
-  auto a = __builtin_amdgcn_permlane16_swap((unsigned)u, opaque_u32((unsigned)u), false, false);
-  auto b = __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), opaque_u32((unsigned)(u >> 32)), false, false);
+  auto a = __builtin_amdgcn_permlane16_swap((unsigned)u, opaque_copy((unsigned)u), false, false);
+  auto b = __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), opaque_copy((unsigned)(u >> 32)), false, false);
   x = __builtin_bit_cast(double, ((uint64_t)(unsigned)b[0] << 32) | (unsigned)a[0]) +
       __builtin_bit_cast(double, ((uint64_t)(unsigned)b[1] << 32) | (unsigned)a[1]);
   u = __builtin_bit_cast(uint64_t, x);
-  auto e = __builtin_amdgcn_permlane32_swap((unsigned)u, opaque_u32((unsigned)u), false, false);
-  auto f = __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), opaque_u32((unsigned)(u >> 32)), false, false);
+  auto e = __builtin_amdgcn_permlane32_swap((unsigned)u, opaque_copy((unsigned)u), false, false);
+  auto f = __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), opaque_copy((unsigned)(u >> 32)), false, false);
   return __builtin_bit_cast(double, ((uint64_t)(unsigned)f[0] << 32) | (unsigned)e[0]) +
          __builtin_bit_cast(double, ((uint64_t)(unsigned)f[1] << 32) | (unsigned)e[1]);
 }
@@ -122,8 +117,9 @@ __device__ __forceinline__ double rows_from64(double x, int c) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// sqrt(q) and 1 / sqrt(q) for q > 0 (a subnormal one too: 1 / sqrt(q) < 2^537): the hardware estimate (about 24 bits) and two
-// Goldschmidt steps, then one correction of the root.  1 / t: the estimate and two Newton steps.
+// sqrt(q) and 1 / sqrt(q) for q > 0 (a subnormal one too: 1 / sqrt(q) < 2^538): the hardware estimate
+// (about 24 bits) and two Goldschmidt steps, then one correction of the root.  1 / t: the estimate and
+// two Newton steps.
 __device__ __forceinline__ void sqrt_rsqrt64(double q, double& root, double& inv) {
   const double y = __builtin_amdgcn_rsq(q);
   double s = q * y, h = 0.5 * y;
@@ -451,14 +447,15 @@ __device__ __forceinline__ d4 tree_load64(const double* src, int lane) {
   r[3] = __builtin_bit_cast(double, ((uint64_t)hi[3] << 32) | hi[2]);
   return r;
 }
-// One wave per inner node of the trees of every problem with NCB column blocks: wave w runs node
-// entry node_begin + w, node node_idx of problem node_prob with children node_l / node_r (>= 0 a
+// One wave per inner node of the trees of every problem with NCB column blocks, an entry each of the
+// tables from node_begin on: node node_idx of problem node_prob with children node_l / node_r (>= 0 a
 // node of the same problem, < 0 its leaf -1 - r).  The entries are in level order over all the
 // problems and workgroups take them as they start (tree_first_entry), so a node's children are
 // leaves (the launch before) or entries of waves that have started.  Every wait is bounded all the
-// same; a timeout sets the problem's ST_STALL bit and the wave still publishes every block.  Leaf triangles are at the problem's slots 0 .. leaves - 1, node outputs
-// at slots leaves + node; flags[(node NCB + q) 2 + k] at the problem's ctr0 (cleared by the factor
-// call's first launch): k = 0 the blocks above the diagonal of column block q, 1 its diagonal block.
+// same; a timeout sets the problem's ST_STALL bit and the wave still publishes every block.  Leaf
+// triangles are at the problem's slots 0 .. leaves - 1, node outputs at slots leaves + node;
+// flags[(node NCB + q) 2 + k] at the problem's ctr0 (cleared by the factor call's first launch): k = 0
+// the blocks above the diagonal of column block q, 1 its diagonal block.
 template <int NCB>
 __global__ void __launch_bounds__(64 * tree_waves_f64(NCB))
 k_tsqr64_tree(int node_begin, int nnodes, const int32_t* __restrict__ node_prob, const int32_t* __restrict__ node_idx,

@@ -14,9 +14,10 @@ namespace qrk {
 
 // One instantiation per column-block count lives in tsqr_mfma_ncb<N>.hip.
 template <int NCB>
-hipError_t launch_tsqr_mfma_n(bool bf16x3, int leaf_begin, int nleaves_cls, const int32_t* leaf_prob, const int32_t* leaf_idx,
-                              const ProbDesc* probs, int n, const float* Red, const double* d, const double* lam,
-                              float* slots, float* RB, const QStore& qs, hipStream_t st);
+hipError_t launch_tsqr_mfma_n(bool bf16x3, int leaf_begin, int nleaves_cls, const int32_t* leaf_prob,
+                              const int32_t* leaf_idx, const ProbDesc* probs, int n, const float* Red,
+                              const double* d, const double* lam, float* slots, float* RB, const QStore& qs,
+                              hipStream_t st);
 
 __global__ void k_zero_ints(int* __restrict__ p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -36,12 +37,13 @@ int tsqr_mfma_slot_floats(int L) {
 
 template <bool BF>
 hipError_t launch_tsqr_queue(int nitems, const int32_t* leaf_prob, const int32_t* leaf_idx, const ProbDesc* probs,
-                             int n, const float* Red, const double* d, const double* lam, float* slots, int* qhead, float* RB, const QStore& qs, int grid, hipStream_t st);
+                             int n, const float* Red, const double* d, const double* lam, float* slots, int* qhead,
+                             float* RB, const QStore& qs, int grid, hipStream_t st);
 
 hipError_t launch_tsqr_mfma(bool bf16x3, const int* cls_begin, const int* cls_count, int queue_begin, bool use_queue,
-                            int cus,
-                            const int32_t* leaf_prob, const int32_t* leaf_idx, const ProbDesc* probs, int n,
-                            const float* Red, const double* d, const double* lam, float* slots, int64_t nctr, int* qhead, float* RB, const QStore& qs, hipStream_t st) {
+                            int cus, const int32_t* leaf_prob, const int32_t* leaf_idx, const ProbDesc* probs, int n,
+                            const float* Red, const double* d, const double* lam, float* slots, int64_t nctr,
+                            int* qhead, float* RB, const QStore& qs, hipStream_t st) {
   // the merge-tree flags and the queue head are cleared by the factor call's first per-block
   // QR launch
   if (nctr < 1) return hipErrorInvalidValue;

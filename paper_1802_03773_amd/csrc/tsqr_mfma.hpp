@@ -41,14 +41,6 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float f_of(unsigned u) { return __builtin_bit_cast(float, u); }
 __device__ __forceinline__ unsigned u_of(float x) { return __builtin_bit_cast(unsigned, x); }
 
-// A copy of x that the compiler cannot identify with x (an empty asm on a register;
-// no memory is touched).  The permlane swaps need two distinct operands.
-__device__ __forceinline__ unsigned opaque_copy(unsigned x) {
-  unsigned y = x;
-  asm volatile("" : "+v"(y));
-  return y;
-}
-
 // Sum over the four 16-lane rows of the wave (lanes l, l^16, l^32, l^48), in every lane.
 // permlane16_swap exchanges the odd rows of its first operand with the even rows of
 // the second, permlane32_swap the upper half of the first with the lower half of the
@@ -572,8 +564,8 @@ __device__ __forceinline__ void tsqr_leaf(int pi, int leaf, const ProbDesc* __re
 
 // Block rows of the running triangle the plain leaf keeps in registers (the rest in LDS): all
 // up to 3 column blocks; none at 4, 5 and 7 and the first at 6 and 8, which frees the registers of
-// the taller tiles (leaf_tile_rows).  20 KiB of LDS per wave at 4 blocks, 15 KiB at 6, 30 KiB at 5
-// and 28 KiB at 7 and 8: with the staging at most 152 KiB per workgroup.
+// the taller tiles (leaf_tile_rows).  10 KiB of LDS per wave at 4 blocks, 15 KiB at 5
+// and 6, 28 KiB at 7 and 8: with the staging at most 152 KiB per workgroup.
 constexpr int leaf_lds_rows(int ncb) {
   return ncb <= 3 ? ncb : (ncb == 6 || ncb == 8 ? 1 : 0);
 }
@@ -671,7 +663,8 @@ __device__ __forceinline__ void tsqr_queue_loop(int nitems, const int32_t* __res
   const int lane = threadIdx.x & 63;
   float* lds = lds_all[threadIdx.x >> 6];
   // the triangle rows in LDS, one array for every width (the largest need is that of 6 or 5 blocks)
-  constexpr int kRl = KEEP ? 1 : 256 * (LeafTri<5>::blocks > LeafTri<6>::blocks ? LeafTri<5>::blocks : LeafTri<6>::blocks);
+  constexpr int kMost = LeafTri<5>::blocks > LeafTri<6>::blocks ? LeafTri<5>::blocks : LeafTri<6>::blocks;
+  constexpr int kRl = KEEP ? 1 : 256 * kMost;
   static_assert(LeafTri<4>::blocks <= LeafTri<5>::blocks, "the queue's LDS rows");
   __shared__ float rl_all[4][kRl];
   float* rl = rl_all[threadIdx.x >> 6];
@@ -702,7 +695,8 @@ template <bool BF>
 __global__ void __launch_bounds__(256)
 k_tsqr_queue(int nitems, const int32_t* __restrict__ leaf_prob, const int32_t* __restrict__ leaf_idx,
              const ProbDesc* __restrict__ probs, int n, const float* __restrict__ Red, const double* __restrict__ d,
-             const double* __restrict__ lamv, float* __restrict__ slots, int* __restrict__ qhead, float* __restrict__ RBall) {
+             const double* __restrict__ lamv, float* __restrict__ slots, int* __restrict__ qhead,
+             float* __restrict__ RBall) {
   tsqr_queue_loop<BF, false>(nitems, leaf_prob, leaf_idx, probs, n, Red, d, lamv, slots, qhead, RBall,
                              QStore());
 }
@@ -717,8 +711,8 @@ k_tsqr_queue_keep(int nitems, const int32_t* __restrict__ leaf_prob, const int32
 
 template <int NCB, int NRB>
 hipError_t launch_tsqr_mfma_ncb(bool bf16x3, int leaf_begin, int nleaves_cls, const int32_t* leaf_prob,
-                                const int32_t* leaf_idx, const ProbDesc* probs, int n, const float* Red, const double* d,
-                                const double* lam, float* slots, float* RB, const QStore& qs,
+                                const int32_t* leaf_idx, const ProbDesc* probs, int n, const float* Red,
+                                const double* d, const double* lam, float* slots, float* RB, const QStore& qs,
                                 hipStream_t st) {
   // the plain leaves stream tiles of leaf_tile_rows rows, the leaves that store Q those of
   // leaf_tile_rows_keep (the stored Q's tile count per leaf)

@@ -6,7 +6,8 @@ namespace qrk {
 
 template <bool BF>
 hipError_t launch_tsqr_queue(int nitems, const int32_t* leaf_prob, const int32_t* leaf_idx, const ProbDesc* probs,
-                             int n, const float* Red, const double* d, const double* lam, float* slots, int* qhead, float* RB, const QStore& qs, int grid, hipStream_t st);
+                             int n, const float* Red, const double* d, const double* lam, float* slots, int* qhead,
+                             float* RB, const QStore& qs, int grid, hipStream_t st);
 
 template <>
 hipError_t launch_tsqr_queue<true>(int nitems, const int32_t* leaf_prob, const int32_t* leaf_idx, const ProbDesc* probs,

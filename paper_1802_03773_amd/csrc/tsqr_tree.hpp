@@ -137,10 +137,10 @@ __device__ __forceinline__ f4 tree_load_block(const float* src, int lane) {
   return __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, 0, kCoherent);
 }
 
-// One wave per inner node of the trees of every problem with NCB column blocks: wave w runs entry
-// tn.begin + w, node idx of problem prob with children l / r (>= 0 a node of the same problem, < 0 its
-// leaf -1 - r).  The entries are in level order over all the problems.  Leaf triangles are at slots 0 .. leaves-1 of the
-// problem, node outputs at slots leaves + node; flags[(node * NCB + q) * 2] marks column block
+// One wave per inner node of the trees of every problem with NCB column blocks, an entry each of the
+// tables from tn.begin on: node idx of problem prob with children l / r (>= 0 a node of the same
+// problem, < 0 its leaf -1 - r).  The entries are in level order over all the problems.  Leaf
+// triangles are at slots 0 .. leaves - 1 of the problem, node outputs at slots leaves + node; flags[(node * NCB + q) * 2] marks column block
 // q of a node's output as published above the diagonal, flags[(node * NCB + q) * 2 + 1] its
 // diagonal block.  A root (a problem's last node) writes R_B | c_B row-major.  KEEP (the stored Q):
 // node k's kept panels are written to qs.qn + qn0 + k * TreeKeep<NCB>::total at its end.
