@@ -292,9 +292,10 @@ qrk_status assign_leaves(qrk_handle h) {
                                    : std::max((double)tile, rows_cls[c] / 4096.0);
         per *= h->leaf_scale;
       }
-      // (float64 leaves are counted by the rows they stream: the damping rows are the first one's start)
-      const int64_t def = std::max<int64_t>(
-          1, std::min<int64_t>((int64_t)std::ceil((double)(f64 ? D.M : D.M + D.nB) / std::max(per, 1.0)), 1024));
+      // (float64: rows that fit one leaf are one leaf's, whatever the damping rows, which are only its start)
+      const int64_t rows = f64 && (double)D.M <= per ? D.M : D.M + D.nB;
+      const int64_t def =
+          std::max<int64_t>(1, std::min<int64_t>((int64_t)std::ceil((double)rows / std::max(per, 1.0)), 1024));
       D.leaves = (int)(h->leaves > 0 ? h->leaves : def);
       D.rows_per_leaf = std::max<int64_t>(1, ceil_div(D.M, D.leaves));
     }
