@@ -315,11 +315,11 @@ k_bgivens_s(int P, int64_t M, int64_t N, const int32_t* __restrict__ row_start, 
   // damping values of the lanes' next rows: block s / RING of columns is current, the lanes that
   // retire in it take their row of the next block (past the last column the last one's, so that no
   // lane divides by zero).  Their size: the rotation needs pivots >= 0, and a row's sign is free; taken
-  // where the value is used: taken at the load, every block waits for its load (807 columns: W = 22,
-  // float32, 300 problems 1,109 us against 1,081; W = 18, float64, 22 problems 1,209 against 1,146).
+  // after the conversion: taken at the load, every block waits for its load (300 problems of 807 columns,
+  // W = 18: 916 us against 893 in float32, 1,347 against 1,308 in float64).
   auto load_d = [&](int64_t col) -> double { return dd[col < N ? col : N - 1]; };
-  Rw[0] = (T)(sl * fabs(load_d(lane)));
-  T dnext = (T)(sl * fabs(load_d((int64_t)RING + lane)));
+  Rw[0] = fabs((T)(sl * load_d(lane)));
+  T dnext = fabs((T)(sl * load_d((int64_t)RING + lane)));
   double dload = load_d((int64_t)2 * RING + lane);  // converted when it is needed
   T piv = T(1), pc = T(0);  // pivot and c of the row this lane retired in this block
   read_next();
@@ -383,7 +383,7 @@ k_bgivens_s(int P, int64_t M, int64_t N, const int32_t* __restrict__ row_start, 
       }
       if (!enter && (s & (RING - 1)) == 0) {
         flush((int64_t)s - RING, RING);
-        dnext = (T)(sl * fabs(dload));
+        dnext = fabs((T)(sl * dload));
         dload = load_d((int64_t)s + 2 * RING + lane);
       }
     }
